@@ -21,6 +21,7 @@
 // contraction.
 #include "lk_internal.h"
 
+#include <climits>
 #include <type_traits>
 
 namespace lkmi {
@@ -665,6 +666,18 @@ __device__ __forceinline__ BatchItem load_item(const BatchItem *items, int i)
     it.first_wave = q->first_wave;
     it.limit = q->limit;
     return it;
+}
+
+// The item of wavefront `wave`: the last of items [lo, n) whose first
+// wavefront is not past it.
+__device__ __forceinline__ int find_item(const BatchItem *items, int lo, int n, int wave)
+{
+    int hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (as_constant(items)[mid].first_wave <= wave) lo = mid; else hi = mid - 1;
+    }
+    return uniform_i(lo);
 }
 
 __device__ __forceinline__ LevelDesc uniform_level(const LevelDesc &d)
@@ -1384,10 +1397,77 @@ __device__ __forceinline__ void finish_level0(const LaneCfg &lc, int win, float 
         pr.status = LK_LOST_OOB;
 }
 
+// A rectangle of the target level in wave-private LDS, M pixels around the taps
+// of one expected window each way: entry (c, r) holds the level at (x0 + c,
+// y0 + r) clamped to it (bilinear taps replicate the edges).
+template <class G>
+struct TapRegion {
+    static constexpr int M = G::WMAX <= 21 ? 5 : 4;
+    static constexpr int RW = G::TW + 2 * M, RH = G::TH + 2 * M, N = RW * RH;
+    static_assert(N <= G::LDS, "the region takes the place of the dead template");
+    int x0, y0;
+
+    // expected first tap of the window at (bx, by)
+    template <int KIND>
+    __device__ __forceinline__ void load(const Plane &P, int bx, int by, int lane, float *lds)
+    {
+        x0 = bx - M;
+        y0 = by - M;
+        constexpr int es = KIND == K_U8 ? 1 : (KIND == K_F16 ? 2 : 4);
+        constexpr int K = (N + kWave - 1) / kWave;
+        float v[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int e = min(lane + k * kWave, N - 1), r = e / RW, c = e - r * RW;
+            v[k] = bload_at<KIND>(P, (clampi(y0 + r, 0, P.h - 1) * P.pitch + clampi(x0 + c, 0, P.w - 1)) * es, 0);
+        }
+        wave_lds_sync();          // the reads of what the region replaces are done
+#pragma unroll
+        for (int k = 0; k < K; ++k) lds[min(lane + k * kWave, N - 1)] = v[k];
+        wave_lds_sync();
+    }
+    // the window whose first tap is (bx, by) lies in the region
+    __device__ __forceinline__ bool holds(int bx, int by) const
+    {
+        return bx >= x0 && bx <= x0 + 2 * M && by >= y0 && by <= y0 + 2 * M;
+    }
+    // this lane's taps of that window, as load_lane_taps returns them
+    __device__ __forceinline__ void taps(const float *lds, int bx, int by, const LaneCfg &lc,
+                                         float (&t)[G::R + 1][G::CW + 1]) const
+    {
+        static_assert(G::CW == 1, "one window column per lane");
+        const float *q = lds + (by - y0 + lc.r0) * RW + (bx - x0 + lc.c0);
+#pragma unroll
+        for (int i = 0; i <= G::R; ++i) {
+            t[i][0] = q[i * RW];
+            t[i][1] = q[i * RW + 1] - q[i * RW];
+        }
+    }
+};
+
+// What a level hands to the next finer one when every level of a keypoint has
+// a wavefront of its own (in LDS, one slot per level).
+struct Baton {
+    int status;
+    float gx, gy;               // flow for the next finer level (status LK_OK, level >= 1)
+    float ox, oy, fx, fy, res;  // the pass's result (a lost status, or level 0)
+};
+
 // One coarse-to-fine pass of pyramid I (template) into pyramid J (target).
-template <int ST, class G>
+// LV (own < 0: off): the levels of the pass belong to the wavefronts of one
+// workgroup, this one's is `own`.  A level's template and normal matrix depend
+// on the point alone, so every wavefront forms its own at once and then waits
+// for the coarser level's flow; wavefront `own` passes own workgroup barriers
+// after its turn and L - 1 - own before it, one per level in all.  Every
+// wavefront returns the pass's result.  While it waits, a wavefront brings the
+// target taps around the expected window into LDS: (aheadx, aheady) is the
+// flow to expect at level 0; with `refine` a level takes that of the level two
+// above it instead, once known.  The expectation moves no result.
+template <int ST, class G, bool LV = false>
 __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, float py, float gx, float gy,
-                               const TrackArgs &a, const LaneCfg &lc, int lane, float *lds, int32_t *iters)
+                               const TrackArgs &a, const LaneCfg &lc, int lane, float *lds, int32_t *iters,
+                               int own = -1, Baton *baton = nullptr, float aheadx = 0.0f, float aheady = 0.0f,
+                               bool refine = false)
 {
     constexpr int R = G::R, CW = G::CW;
     const int win = G::EXACT ? G::WMAX : a.win, h = (win - 1) >> 1, L = a.levels;
@@ -1399,13 +1479,26 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
     const int w0 = L0.w, h0 = L0.h;
     if (!(px >= 0.0f && px <= (float)(w0 - 1) && py >= 0.0f && py <= (float)(h0 - 1))) {
         pr.status = LK_LOST_OOB;
-        return pr;
+        return pr;                 // (every wavefront of the point)
     }
+    // the end of this wavefront's part of the pass, level l
+    auto leave = [&](int l) {
+        if constexpr (LV) {
+            if (lc.lane0) baton[l] = Baton{pr.status, gx, gy, pr.ox, pr.oy, pr.fx, pr.fy, pr.res};
+            for (int t = 0; t <= l; ++t) __syncthreads();
+            const Baton &e = baton[0];
+            pr.status = uniform_i(e.status);
+            pr.ox = uniform_f(e.ox); pr.oy = uniform_f(e.oy);
+            pr.fx = uniform_f(e.fx); pr.fy = uniform_f(e.fy);
+            pr.res = uniform_f(e.res);
+        }
+        return pr;
+    };
     float T[R][CW], GX[R][CW], GY[R][CW];
     float dx = 0.0f, dy = 0.0f;
     float cfx = 0.0f, cfy = 0.0f;
     int cix = 0, ciy = 0;
-    for (int l = L - 1; l >= 0; --l) {
+    for (int l = LV ? own : L - 1; l >= 0; --l) {
         const LevelDesc LI = uniform_level(I.lv[l]);
         const LevelDesc LJ = uniform_level(J.lv[l]);
         const float cxs = ldexpf(px, -l), cys = ldexpf(py, -l);   // exact scaling
@@ -1470,21 +1563,21 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
         // lambda_max, which has no cancellation, in float.
         const double ddet = (double)Gxx * (double)Gyy - (double)Gxy * (double)Gxy;
         const float det = (float)ddet;
-        {
-            // lambda_min / (N_w 255^2) >= min_eig, as det >= min_eig N_w 255^2
-            // lambda_max with lambda_max > 0 (a flat window, lambda_max = 0, and
-            // NaN fail); the uniform scalar work runs on the vector ALU, so the
-            // hardware square root (1 ulp) replaces the refined one and no
-            // division is needed
-            const float lmax =
-                0.5f * ((Gxx + Gyy) + __builtin_amdgcn_sqrtf((Gxx - Gyy) * (Gxx - Gyy) + 4.0f * Gxy * Gxy));
-            if (!(lmax > 0.0f && det >= a.min_eig * (nw * 65025.0f) * lmax)) {
-                pr.status = LK_LOST_EIG;
-                pr.ox = ldexpf((float)cix + (cfx + gx), l);
-                pr.oy = ldexpf((float)ciy + (cfy + gy), l);
-                return pr;
-            }
-        }
+        // lambda_min / (N_w 255^2) >= min_eig, as det >= min_eig N_w 255^2
+        // lambda_max with lambda_max > 0 (a flat window, lambda_max = 0, and
+        // NaN fail); the uniform scalar work runs on the vector ALU, so the
+        // hardware square root (1 ulp) replaces the refined one and no
+        // division is needed
+        const float lmax = 0.5f * ((Gxx + Gyy) + __builtin_amdgcn_sqrtf((Gxx - Gyy) * (Gxx - Gyy) + 4.0f * Gxy * Gxy));
+        const bool textured = lmax > 0.0f && det >= a.min_eig * (nw * 65025.0f) * lmax;
+        auto lost_eig = [&]() {
+            pr.status = LK_LOST_EIG;
+            pr.ox = ldexpf((float)cix + (cfx + gx), l);
+            pr.oy = ldexpf((float)ciy + (cfy + gy), l);
+            return leave(l);
+        };
+        if constexpr (!LV)
+            if (!textured) return lost_eig();
         const float rdet = __builtin_amdgcn_rcpf(det);      // 1 ulp
         const float lox = (float)(-h - cix), hix = (float)(LJ.w - 1 + h - cix);
         const float loy = (float)(-h - ciy), hiy = (float)(LJ.h - 1 + h - ciy);
@@ -1498,7 +1591,13 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
         // instructions, not arithmetic, bound them), which must not start on
         // the level's last row
         constexpr bool PAIR = ST == LK_STORAGE_F16 && G::CW == 1;
+        TapRegion<G> region{INT_MIN / 2, INT_MIN / 2};     // (holds no window)
         auto load_target = [&](int bx, int by) {
+            if constexpr (LV && ST == LK_STORAGE_F32)
+                if (region.holds(bx - h, by - h)) {
+                    region.taps(lds, bx - h, by - h, lc, jt);
+                    return;
+                }
             const bool inside = bx - h >= 0 && by - h >= 0 && bx - h + G::EXX < PJ.w &&
                                 by - h + G::EXY < PJ.h - (PAIR ? 1 : 0);
             if (l == 0) load_lane_taps<G, K_U8, PAIR>(PJ, bx - h + lc.c0, by - h + lc.r0, inside, jt);
@@ -1506,6 +1605,34 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
                 load_lane_taps<G, K_F16, PAIR>(PJ, bx - h + lc.c0, by - h + lc.r0, inside, jt);
             else load_lane_taps<G, K_F32>(PJ, bx - h + lc.c0, by - h + lc.r0, inside, jt);
         };
+        if constexpr (LV) {
+            int t = L - 1;
+            if (ST == LK_STORAGE_F32 && l < L - 1) {
+                float ex = ldexpf(aheadx, -l), ey = ldexpf(aheady, -l);
+                if (refine && l < L - 2) {
+                    for (; t > l + 1; --t) __syncthreads();
+                    ex = 2.0f * uniform_f(baton[l + 2].gx);
+                    ey = 2.0f * uniform_f(baton[l + 2].gy);
+                }
+                // clamped before the conversion: any guess is accepted, and a
+                // lost coarser level's flow has no meaning
+                const int bx = cix + (int)fminf(fmaxf(floorf(cfx + ex), -(float)LJ.w), (float)LJ.w);
+                const int by = ciy + (int)fminf(fmaxf(floorf(cfy + ey), -(float)LJ.h), (float)LJ.h);
+                if (l == 0) region.template load<K_U8>(PJ, uniform_i(bx) - h, uniform_i(by) - h, lane, lds);
+                else region.template load<K_F32>(PJ, uniform_i(bx) - h, uniform_i(by) - h, lane, lds);
+            }
+            for (; t > l; --t) __syncthreads();
+            if (l < L - 1) {
+                const Baton &c = baton[l + 1];
+                if (uniform_i(c.status) != LK_OK) {
+                    pr.status = uniform_i(c.status);
+                    pr.ox = uniform_f(c.ox); pr.oy = uniform_f(c.oy);
+                    return leave(l);
+                }
+                gx = uniform_f(c.gx); gy = uniform_f(c.gy);
+            }
+            if (!textured) return lost_eig();
+        }
         // The taps of the first estimate are loaded before the iterations
         // (its integer part clamped to the level's range: an estimate outside
         // ends the pass before any tap is read, and the clamped loads stay in
@@ -1583,12 +1710,13 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
             pr.ox = ldexpf((float)cix + ux, l);
             pr.oy = ldexpf((float)ciy + uy, l);
             if (iters && lc.lane0) iters[l] = k - 1;
-            return pr;
+            return leave(l);
         }
         if (iters && lc.lane0) iters[l] = k;
         if (l > 0) {
             gx = 2.0f * (gx + dx);
             gy = 2.0f * (gy + dy);
+            if constexpr (LV) return leave(l);
             continue;
         }
         if constexpr (G::R <= 7 && ST == LK_STORAGE_F32) {
@@ -1616,7 +1744,16 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
         load_lane_taps<G, K_U8>(PJ, bx - h + lc.c0, by - h + lc.r0, inside, jt);
         finish_level0<G>(lc, win, nw, T, jt, ux, uy, fux, fuy, cix, ciy, cfx, cfy, LJ, pr);
     }
-    return pr;
+    return leave(0);
+}
+
+// The forward-backward check of a point tracked by the forward pass f.
+__device__ __forceinline__ int fb_status(const PassResult &f, const PassResult &b, float px, float py, float thresh)
+{
+    if (b.status != LK_OK) return LK_LOST_FB;
+    // p' - p = (q - p) + backward flow; q - p is exact for nearby floats
+    const float vx = (f.ox - px) + b.fx, vy = (f.oy - py) + b.fy;
+    return sqrtf(vx * vx + vy * vy) > thresh ? LK_LOST_FB : LK_OK;
 }
 
 template <int ST, class G>
@@ -1625,7 +1762,8 @@ __device__ void track_point(const PyrDesc &prev, const PyrDesc &next, const Trac
 {
     const LaneCfg lc = lane_cfg<G>(a.win, lane);
     const int L = a.levels;
-    const float px = uniform_f(a.pts[2 * idx]), py = uniform_f(a.pts[2 * idx + 1]);
+    // (scalar loads: no keypoint's wavefront but its own may write its entry)
+    const float px = as_constant(a.pts)[2 * idx], py = as_constant(a.pts)[2 * idx + 1];
     float gx = 0.0f, gy = 0.0f;
     if (a.use_guess) {
         gx = ldexpf(uniform_f(a.guess[2 * idx]) - px, -(L - 1));
@@ -1650,15 +1788,47 @@ __device__ void track_point(const PyrDesc &prev, const PyrDesc &next, const Trac
         } else {
             b = run_pass<ST, G>(next, prev, f.ox, f.oy, 0.0f, 0.0f, a, lc, lane, lds, itb);
         }
-        if (b.status != LK_OK) {
-            status = LK_LOST_FB;
-        } else {
-            // p' - p = (q - p) + backward flow; q - p is exact for nearby floats
-            const float vx = (f.ox - px) + b.fx, vy = (f.oy - py) + b.fy;
-            if (sqrtf(vx * vx + vy * vy) > a.fb_thresh) status = LK_LOST_FB;
-        }
+        status = fb_status(f, b, px, py, a.fb_thresh);
     }
     if (lane == 0) {
+        a.out_pts[2 * idx] = f.ox;
+        a.out_pts[2 * idx + 1] = f.oy;
+        a.status[idx] = (uint8_t)status;
+        a.residual[idx] = f.res;
+    }
+}
+
+// track_point with a wavefront per level: the a.levels wavefronts of the
+// workgroup call it together, wavefront `own` with LDS and baton of its own
+// workgroup.  Same operations on the same operands as track_point, so the
+// same bits.
+template <int ST, class G>
+__device__ __forceinline__ void track_point_levels(const PyrDesc &prev, const PyrDesc &next, const TrackArgs &a, int idx,
+                                                   int lane, int own, float *lds, Baton *baton)
+{
+    const LaneCfg lc = lane_cfg<G>(a.win, lane);
+    const int L = a.levels;
+    // (scalar loads: no keypoint's wavefront but its own may write its entry)
+    const float px = as_constant(a.pts)[2 * idx], py = as_constant(a.pts)[2 * idx + 1];
+    float gx = 0.0f, gy = 0.0f;
+    if (a.use_guess) {
+        gx = ldexpf(uniform_f(a.guess[2 * idx]) - px, -(L - 1));
+        gy = ldexpf(uniform_f(a.guess[2 * idx + 1]) - py, -(L - 1));
+    }
+    // each wavefront clears and writes the counts of its own level only
+    int32_t *itp = a.iters ? a.iters + (size_t)idx * 2 * L : nullptr;
+    if (itp && lc.lane0) itp[own] = itp[L + own] = 0;
+    PassResult f, b;
+    [[clang::always_inline]] f = run_pass<ST, G, true>(prev, next, px, py, gx, gy, a, lc, lane, lds, itp, own, baton,
+                                                            ldexpf(gx, L - 1), ldexpf(gy, L - 1), true);
+    int status = f.status;
+    if (status == LK_OK && a.fb_thresh > 0.0f) {
+        int32_t *itb = itp ? itp + L : nullptr;
+        [[clang::always_inline]] b =
+            run_pass<ST, G, true>(next, prev, f.ox, f.oy, 0.0f, 0.0f, a, lc, lane, lds, itb, own, baton, -f.fx, -f.fy);
+        status = fb_status(f, b, px, py, a.fb_thresh);
+    }
+    if (own == 0 && lane == 0) {
         a.out_pts[2 * idx] = f.ox;
         a.out_pts[2 * idx + 1] = f.oy;
         a.status[idx] = (uint8_t)status;
@@ -1693,13 +1863,7 @@ void k_track_batched(const BatchItem *items, int n_items, TrackArgs a)
     const int wib = threadIdx.x >> 6;
     const int wave = uniform_i(xcd_block(blockIdx.x, gridDim.x) * G::WPB + wib);
     if (wave >= a.n) return;
-    int lo = 0, hi = n_items - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (as_constant(items)[mid].first_wave <= wave) lo = mid; else hi = mid - 1;
-    }
-    lo = uniform_i(lo);
-    const BatchItem it = load_item(items, lo);
+    const BatchItem it = load_item(items, find_item(items, 0, n_items, wave));
     if (it.limit && wave - it.first_wave >= *as_constant(it.limit)) return;   // past the item's live count
     const int idx = (int)(it.pt_offset + (wave - it.first_wave));
     if constexpr (G::CW == 1) {
@@ -1707,6 +1871,42 @@ void k_track_batched(const BatchItem *items, int n_items, TrackArgs a)
     } else {
         track_point<ST, G>(*it.prev, *it.next, a, idx, threadIdx.x & (kWave - 1), s_lds + wib * G::LDS);
     }
+}
+
+// A wavefront per pyramid level (2 to kLevelWaves of them), one keypoint per
+// workgroup, for launches that leave the chip short of wavefronts.  What
+// bounds such a launch is one keypoint's chain of dependent steps, level after
+// level: the template's loads, its normal matrix, the taps, the iterations.
+// The templates of all levels need only the point, so here they run side by
+// side and only the iterations stay in sequence.
+constexpr int kLevelWaves = 4;
+// Wavefronts per SIMD these kernels are built for.
+template <int ST, class G>
+constexpr int kLevelOcc = G::R <= 7 ? (ST == LK_STORAGE_F16 ? 6 : 4) : (ST == LK_STORAGE_F16 ? 3 : 2);
+
+template <int ST, class G>
+__global__ __launch_bounds__(kLevelWaves * 64) __attribute__((amdgpu_waves_per_eu(kLevelOcc<ST, G>)))
+void k_track_levels(const PyrDesc *prev, const PyrDesc *next, TrackArgs a)
+{
+    extern __shared__ float s_lds[];               // G::LDS floats a wavefront
+    __shared__ Baton s_baton[kLevelWaves];
+    const int own = uniform_i((int)threadIdx.x >> 6);
+    const int idx = xcd_block(blockIdx.x, gridDim.x);
+    track_point_levels<ST, G>(*prev, *next, a, idx, threadIdx.x & (kWave - 1), own, s_lds + own * G::LDS, s_baton);
+}
+
+template <int ST, class G>
+__global__ __launch_bounds__(kLevelWaves * 64) __attribute__((amdgpu_waves_per_eu(kLevelOcc<ST, G>)))
+void k_track_batched_levels(const BatchItem *items, int n_items, TrackArgs a)
+{
+    extern __shared__ float s_lds[];               // G::LDS floats a wavefront
+    __shared__ Baton s_baton[kLevelWaves];
+    const int own = uniform_i((int)threadIdx.x >> 6);
+    const int wave = xcd_block(blockIdx.x, gridDim.x);
+    const BatchItem it = load_item(items, find_item(items, 0, n_items, wave));
+    if (it.limit && wave - it.first_wave >= *as_constant(it.limit)) return;   // past the item's live count
+    const int idx = (int)(it.pt_offset + (wave - it.first_wave));
+    track_point_levels<ST, G>(*it.prev, *it.next, a, idx, threadIdx.x & (kWave - 1), own, s_lds + own * G::LDS, s_baton);
 }
 
 // Persistent form: a fixed grid whose wavefronts take chunks of `chunk`
@@ -1738,12 +1938,7 @@ void k_track_persist(const BatchItem *items, int n_items, TrackArgs a, int *coun
             for (int wave = w0; wave < w1; ++wave) {
                 // items are ordered by first_wave: continue the search from
                 // the previous keypoint's item
-                int hi = n_items - 1;
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (as_constant(items)[mid].first_wave <= wave) lo = mid; else hi = mid - 1;
-                }
-                lo = uniform_i(lo);
+                lo = find_item(items, lo, n_items, wave);
                 const BatchItem it = load_item(items, lo);
                 if (it.limit && wave - it.first_wave >= *as_constant(it.limit)) continue;
                 const int idx = (int)(it.pt_offset + (wave - it.first_wave));
@@ -1820,9 +2015,32 @@ __global__ __launch_bounds__(kThreads) void k_read_level(LevelDesc lv, int kind,
 template <class G>
 inline unsigned blocks_for(long waves) { return (unsigned)((waves + G::WPB - 1) / G::WPB); }
 
+// Whether a launch of n keypoints takes a wavefront per level: when all their
+// workgroups are resident at once.  Up to there the side-by-side templates
+// shorten the launch; past it the waiting wavefronts hold room that a second
+// round of workgroups needs.  Measured (us, wavefront per level against one
+// wavefront per keypoint, back to back): 21x21, 3 levels, float32, no backward
+// pass: 9.4 / 12.5 at 150 keypoints, 12.0 / 15.0 at 1280 (the limit), 17.4 /
+// 15.6 at 1500; 4 levels with the backward pass 21 / 31 at 150, 28 / 37 at
+// 1000, 42 / 38 at 1280 (limit 1024); 31x31, 4 levels, backward pass, binary16
+// 26 / 37 at 150, 34 / 46 at 768 (the limit), 53 / 46 at 1000; 31x31, float32,
+// forward only 16 / 33 at 150, 18 / 35 at 500, 32 / 37 at 600 (limit 512).
+constexpr int kCUs = 256;
+
+template <int ST, class G>
+inline bool use_level_waves(const TrackArgs &a)
+{
+    return a.levels >= 2 && a.levels <= kLevelWaves && a.n <= kCUs * (4 * kLevelOcc<ST, G> / a.levels);
+}
+
 template <int ST, class G>
 hipError_t launch_track_g(const PyrDesc *prev, const PyrDesc *next, const TrackArgs &a, hipStream_t s)
 {
+    if (use_level_waves<ST, G>(a)) {
+        hipLaunchKernelGGL((k_track_levels<ST, G>), dim3(a.n), dim3(a.levels * 64), a.levels * G::LDS * sizeof(float),
+                           s, prev, next, a);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL((k_track<ST, G>), dim3(blocks_for<G>(a.n)), dim3(G::WPB * 64), 0, s, prev, next, a);
     return hipGetLastError();
 }
@@ -1839,9 +2057,15 @@ hipError_t launch_track_st(const PyrDesc *prev, const PyrDesc *next, const Track
     }
 }
 
+// by_level: the launch may take a wavefront per level (no shape was asked for).
 template <int ST, class G>
-hipError_t launch_track_batched_g(const BatchItem *items, int n_items, const TrackArgs &a, hipStream_t s)
+hipError_t launch_track_batched_g(const BatchItem *items, int n_items, const TrackArgs &a, hipStream_t s, bool by_level)
 {
+    if (by_level && use_level_waves<ST, G>(a)) {
+        hipLaunchKernelGGL((k_track_batched_levels<ST, G>), dim3(a.n), dim3(a.levels * 64),
+                           a.levels * G::LDS * sizeof(float), s, items, n_items, a);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL((k_track_batched<ST, G>), dim3(blocks_for<G>(a.n)), dim3(G::WPB * 64), 0, s, items, n_items, a);
     return hipGetLastError();
 }
@@ -1851,13 +2075,13 @@ hipError_t launch_track_batched_st(const BatchItem *items, int n_items, const Tr
 {
     switch (choose_layout(a.win)) {
     case LAYOUT_W21:
-        if (a.win != GeoW21X::WMAX) return wpg <= 1 ? launch_track_batched_g<ST, GeoW21>(items, n_items, a, s)
+        if (a.win != GeoW21X::WMAX) return wpg <= 1 ? launch_track_batched_g<ST, GeoW21>(items, n_items, a, s, wpg == 0)
                                                      : hipErrorInvalidValue;
-        if (wpg == 2) return launch_track_batched_g<ST, GeoW21X2>(items, n_items, a, s);
-        if (wpg == 4) return launch_track_batched_g<ST, GeoW21X4>(items, n_items, a, s);
-        return wpg <= 1 ? launch_track_batched_g<ST, GeoW21X>(items, n_items, a, s) : hipErrorInvalidValue;
+        if (wpg == 2) return launch_track_batched_g<ST, GeoW21X2>(items, n_items, a, s, wpg == 0);
+        if (wpg == 4) return launch_track_batched_g<ST, GeoW21X4>(items, n_items, a, s, wpg == 0);
+        return wpg <= 1 ? launch_track_batched_g<ST, GeoW21X>(items, n_items, a, s, wpg == 0) : hipErrorInvalidValue;
     case LAYOUT_W31:
-        return wpg == 0 || wpg == GeoW31::WPB ? launch_track_batched_g<ST, GeoW31>(items, n_items, a, s)
+        return wpg == 0 || wpg == GeoW31::WPB ? launch_track_batched_g<ST, GeoW31>(items, n_items, a, s, wpg == 0)
                                                : hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
