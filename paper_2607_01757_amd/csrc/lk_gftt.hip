@@ -24,8 +24,13 @@
 //                  candidates are found from the bucket counts and, inside
 //                  the last bucket a window reaches, by radix selection on the
 //                  96-bit rank key (R bits, then the complemented raster
-//                  index); they are sorted in LDS and accepted 512 at a time
-//                  against the corners taken so far and the occupied points.
+//                  index); they are sorted in LDS and accepted up to 512 at a
+//                  time against the corners taken so far and the occupied points.
+//                  Latency bounds it: one 752x480 frame 58.8 us with a bitonic
+//                  sort, chunks of 512 and windows of exactly 2048, 32.8 us with
+//                  the counting sort (-14), the half first chunk and wider checks
+//                  (-9), three instructions a pair (-3) and windows that end
+//                  where the digits allow; 64 mixed frames 104 -> 77 us.
 //                  The acceptance within a chunk resolves the greedy rule
 //                  exactly (a candidate is taken iff no better candidate that
 //                  is taken lies too close).
@@ -854,7 +859,9 @@ __global__ __launch_bounds__(BLOCK) void k_gftt_bucket(const GfttJob *__restrict
 constexpr int CAPW = kGfttWindow;             // window of peaks sorted in LDS
 constexpr int TG_CELLS = 2048;                // cells of the taken-corner grid, at most
 constexpr int SBLOCK = 1024;                  // threads of the selection workgroup
-constexpr int CHUNK = 512;                    // candidates decided together (the first CHUNK threads)
+constexpr int CHUNK = 512;                    // unblocked candidates decided together, at most
+constexpr int STEPS = 2048;                   // steps of a window's range in the counting sort
+constexpr uint32_t STEP_KEYS = 32;            // keys of one step, at most, for that sort
 constexpr int KPT = 4;                        // keys per thread in flight in the list passes
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
@@ -868,9 +875,10 @@ struct alignas(16) SelSmem {
     int32_t tg_next[kGfttMaxCorners + 16];     // the next index in the same cell
     uint32_t hist[SBLOCK / 64][256];           // one histogram per wavefront
     unsigned long long cmask[CHUNK][CHUNK / 64];   // conflicts with better candidates of the chunk
-    unsigned long long sel[CHUNK / 64], und[CHUNK / 64];
+    unsigned long long sel[CHUNK / 64], und[SBLOCK / 64];
     uint32_t bstart[256], bcnt[256];           // the list range of each bucket
     uint32_t bwsum[4];
+    uint32_t ssum[SBLOCK / 64];               // the counting sort's keys per wavefront of steps
     int32_t bb, be;
     uint32_t wcount, bcount;
     Key bound;
@@ -998,7 +1006,7 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
         // ---- the next window: the best min(CAPW, remaining) candidates,
         // ranks [consumed, consumed + wn) of the descending order
         const int consumed = np - remaining;
-        const int wn = remaining < CAPW ? remaining : CAPW;
+        int wn = remaining < CAPW ? remaining : CAPW;
         if (tid < 256) {
             const int b0 = (int)sm.bstart[tid], b1 = b0 + (int)sm.bcnt[tid];
             if (b0 <= consumed && consumed < b1) sm.bb = tid;
@@ -1015,7 +1023,9 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
         Key low = wn < remaining ? bucket_low : Key{0, 0};
         if (wn < remaining && consumed + wn < (int)(sm.bstart[be] + sm.bcnt[be])) {
             // the window ends inside bucket be: radix selection of its best
-            // `need` eligible keys, by the digits after the bucket's
+            // `need` eligible keys, by the digits after the bucket's, until the
+            // keys above a digit make a window of at least half the capacity
+            // (a full one would take a pass per digit more)
             const uint32_t need_be = (uint32_t)(consumed + wn - max(consumed, (int)sm.bstart[be]));
             uint32_t need = need_be;
             Key prefix = bucket_low;
@@ -1071,6 +1081,12 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
                 const int kept = (int)(need_be - need + sm.bcount);   // bucket keys >= the new prefix
                 __syncthreads();
                 if (whole) break;
+                if (wn - (int)need >= CAPW / 2) {
+                    // without the digit the full window would end in
+                    prefix = key_after_digit(prefix, d);
+                    wn -= (int)need;
+                    break;
+                }
                 if (!filtered && 4 * kept <= nB) {
                     // copy bucket be's eligible keys >= prefix (its lower bytes
                     // are 0) to the spare list, KPT keys per thread in flight
@@ -1131,95 +1147,175 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
         }
         __syncthreads();
         const int wu = min((int)sm.wcount, CAPW);   // the window's keys no taken corner blocks
-        int pw = 1;
-        while (pw < wu) pw <<= 1;
-        // Bitonic sort, descending, of pw slots (keys past wu are 0, below
-        // every key): thread tid holds elements E tid .. E tid + E - 1 in
-        // registers; the compare-exchanges of stride below E stay inside a
-        // thread, those of stride E .. 32 E go to lane tid ^ (stride / E) of
-        // the same wavefront, and only those of stride 64 E and more pass
-        // through LDS (6 barrier pairs for 2048 keys instead of a barrier per
-        // stage).
+        // Descending order by counting: the window's R bits lie in a known range
+        // whose 2048 equal steps hold a key or two each (the density of R
+        // changes little over a window), so a key's place is the number of
+        // keys in higher steps plus the larger ones of its own step, counted
+        // over that step's few keys with the whole rank key.  A step that
+        // holds many (plateaus of equal R) would make that quadratic: such a
+        // window is sorted by the bitonic network below instead.  What bounds
+        // either is latency (one workgroup per frame): 7 barriers here against
+        // 66 dependent stages.
         constexpr int E = CAPW / SBLOCK;
         static_assert(E == 2 || E == 4, "two or four window keys per thread");
+        const unsigned long long r_hi = bounded ? bound.hi : max_bits;
+        const unsigned long long r_lo = low.hi > thr_bits ? low.hi : thr_bits;
+        const int r_sh = max(0, 64 - 11 - (int)__clzll((long long)((r_hi - r_lo) | 1)));
+        uint32_t *step = &sm.hist[0][0];
+        unsigned long long *shi = &sm.cmask[0][0];          // the keys by step
+        uint32_t *slo = reinterpret_cast<uint32_t *>(shi + CAPW);
+        static_assert(CAPW == STEPS && sizeof(sm.hist) >= STEPS * sizeof(uint32_t) &&
+                      sizeof(sm.cmask) >= CAPW * 12, "the counting sort borrows both");
         Key kk[E];
+        uint32_t kd[E], ka[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) step[tid + e * SBLOCK] = 0;
+        __syncthreads();
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int i = E * tid + e;
+            const int i = tid + e * SBLOCK;
             kk[e] = i < wu ? Key{sm.whi[i], sm.wlo[i]} : Key{0, 0};
+            kd[e] = i < wu ? (uint32_t)(STEPS - 1) - (uint32_t)((kk[e].hi - r_lo) >> r_sh) : 0u;
+            ka[e] = i < wu ? atomicAdd(&step[kd[e]], 1u) : 0u;      // arrival in its step
         }
-        // element i keeps the larger key of (i, i ^ stride) iff i is the lower
-        // one of a descending block ((i & size) == 0) or the upper one of an
-        // ascending block
-        auto keep = [&](int e, Key o, int stride, int size) {
-            const int i = E * tid + e;
-            const bool keep_max = ((i & size) == 0) == ((i & stride) == 0);
-            const bool o_less = key_less(o, kk[e]);
-            if (keep_max != o_less) kk[e] = o;
-        };
-        for (int size = 2; size <= pw; size <<= 1) {
-            for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                if (stride >= 64 * E) {
-                    __syncthreads();                     // the last stage's reads are done
+        __syncthreads();
+        uint32_t tsum = 0, c[E];
+        bool crowded = false;
 #pragma unroll
-                    for (int e = 0; e < E; ++e) {
-                        sm.whi[E * tid + e] = kk[e].hi;
-                        sm.wlo[E * tid + e] = kk[e].lo;
-                    }
-                    __syncthreads();
-                    Key o[E];
+        for (int e = 0; e < E; ++e) {
+            c[e] = step[E * tid + e];
+            crowded |= c[e] > STEP_KEYS;
+            tsum += c[e];
+        }
+        uint32_t incl = tsum;
 #pragma unroll
-                    for (int e = 0; e < E; ++e) {
-                        const int j = (E * tid + e) ^ stride;
-                        o[e] = Key{sm.whi[j], sm.wlo[j]};
-                    }
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t t = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += t;
+        }
+        if (lane == 63) sm.ssum[wv] = incl;
+        if (!__syncthreads_or(crowded)) {
+            uint32_t run = incl - tsum;
+            for (int w = 0; w < wv; ++w) run += sm.ssum[w];
 #pragma unroll
-                    for (int e = 0; e < E; ++e) keep(e, o[e], stride, size);
-                } else if (stride >= E) {
-                    // all exchanges in flight before the first use
-                    const int m = stride / E;
-                    Key o[E];
+            for (int e = 0; e < E; ++e) {
+                step[E * tid + e] = run;                   // the step's first place
+                run += c[e];
+            }
+            __syncthreads();
 #pragma unroll
-                    for (int e = 0; e < E; ++e) {
-                        o[e].hi = __shfl_xor(kk[e].hi, m, 64);
-                        o[e].lo = __shfl_xor(kk[e].lo, m, 64);
-                    }
+            for (int e = 0; e < E; ++e)
+                if (tid + e * SBLOCK < wu) {
+                    const uint32_t at = step[kd[e]] + ka[e];
+                    shi[at] = kk[e].hi;
+                    slo[at] = kk[e].lo;
+                }
+            __syncthreads();
+            uint32_t rank[E];
 #pragma unroll
-                    for (int e = 0; e < E; ++e) keep(e, o[e], stride, size);
-                } else {
-                    // inside the thread (the elements of a pair share (i & size))
-                    auto cex = [&](Key &a, Key &b, int i) {
-                        if (key_less(a, b) == ((i & size) == 0)) {
-                            const Key t = a;
-                            a = b;
-                            b = t;
+            for (int e = 0; e < E; ++e) {
+                if (tid + e * SBLOCK >= wu) continue;
+                const uint32_t q0 = step[kd[e]], q1 = kd[e] == STEPS - 1 ? (uint32_t)wu : step[kd[e] + 1];
+                rank[e] = q0;
+                for (uint32_t q = q0; q < q1; ++q) rank[e] += key_less(kk[e], Key{shi[q], slo[q]}) ? 1u : 0u;
+                sm.whi[rank[e]] = kk[e].hi;    // (every thread has its keys in registers)
+                sm.wlo[rank[e]] = kk[e].lo;
+            }
+            __syncthreads();
+        } else {
+            int pw = 1;
+            while (pw < wu) pw <<= 1;
+            // Bitonic sort, descending, of pw slots (keys past wu are 0, below
+            // every key): thread tid holds elements E tid .. E tid + E - 1 in
+            // registers; the compare-exchanges of stride below E stay inside a
+            // thread, those of stride E .. 32 E go to lane tid ^ (stride / E) of
+            // the same wavefront, and only those of stride 64 E and more pass
+            // through LDS (6 barrier pairs for 2048 keys instead of a barrier per
+            // stage).
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int i = E * tid + e;
+                kk[e] = i < wu ? Key{sm.whi[i], sm.wlo[i]} : Key{0, 0};
+            }
+            // element i keeps the larger key of (i, i ^ stride) iff i is the lower
+            // one of a descending block ((i & size) == 0) or the upper one of an
+            // ascending block
+            auto keep = [&](int e, Key o, int stride, int size) {
+                const int i = E * tid + e;
+                const bool keep_max = ((i & size) == 0) == ((i & stride) == 0);
+                const bool o_less = key_less(o, kk[e]);
+                if (keep_max != o_less) kk[e] = o;
+            };
+            for (int size = 2; size <= pw; size <<= 1) {
+                for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                    if (stride >= 64 * E) {
+                        __syncthreads();                     // the last stage's reads are done
+#pragma unroll
+                        for (int e = 0; e < E; ++e) {
+                            sm.whi[E * tid + e] = kk[e].hi;
+                            sm.wlo[E * tid + e] = kk[e].lo;
                         }
-                    };
-                    if constexpr (E == 2) {
-                        cex(kk[0], kk[1], 2 * tid);
+                        __syncthreads();
+                        Key o[E];
+#pragma unroll
+                        for (int e = 0; e < E; ++e) {
+                            const int j = (E * tid + e) ^ stride;
+                            o[e] = Key{sm.whi[j], sm.wlo[j]};
+                        }
+#pragma unroll
+                        for (int e = 0; e < E; ++e) keep(e, o[e], stride, size);
+                    } else if (stride >= E) {
+                        // all exchanges in flight before the first use
+                        const int m = stride / E;
+                        Key o[E];
+#pragma unroll
+                        for (int e = 0; e < E; ++e) {
+                            o[e].hi = __shfl_xor(kk[e].hi, m, 64);
+                            o[e].lo = __shfl_xor(kk[e].lo, m, 64);
+                        }
+#pragma unroll
+                        for (int e = 0; e < E; ++e) keep(e, o[e], stride, size);
                     } else {
-                        if (stride == 2) {
-                            cex(kk[0], kk[2], 4 * tid);
-                            cex(kk[1], kk[3], 4 * tid + 1);
+                        // inside the thread (the elements of a pair share (i & size))
+                        auto cex = [&](Key &a, Key &b, int i) {
+                            if (key_less(a, b) == ((i & size) == 0)) {
+                                const Key t = a;
+                                a = b;
+                                b = t;
+                            }
+                        };
+                        if constexpr (E == 2) {
+                            cex(kk[0], kk[1], 2 * tid);
                         } else {
-                            cex(kk[0], kk[1], 4 * tid);
-                            cex(kk[2], kk[3], 4 * tid + 2);
+                            if (stride == 2) {
+                                cex(kk[0], kk[2], 4 * tid);
+                                cex(kk[1], kk[3], 4 * tid + 1);
+                            } else {
+                                cex(kk[0], kk[1], 4 * tid);
+                                cex(kk[2], kk[3], 4 * tid + 2);
+                            }
                         }
                     }
                 }
             }
-        }
-        __syncthreads();
+            __syncthreads();
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            sm.whi[E * tid + e] = kk[e].hi;
-            sm.wlo[E * tid + e] = kk[e].lo;
+            for (int e = 0; e < E; ++e) {
+                sm.whi[E * tid + e] = kk[e].hi;
+                sm.wlo[E * tid + e] = kk[e].lo;
+            }
+            __syncthreads();
         }
-        __syncthreads();
         // ---- accept in rank order, CHUNK candidates at a time
-        for (int c0 = 0; c0 < wu && nt < max_corners; c0 += CHUNK) {
+        // (a candidate per thread, of which the leading wavefronts with at most
+        // CHUNK unblocked ones in all are decided: their pairs are compared,
+        // so the work grows with the square; while no corner is taken nothing
+        // is blocked and most pairs are compared for nothing, so the first
+        // chunk is half as long)
+        int used = 0;
+        for (int c0 = 0; c0 < wu && nt < max_corners; c0 += used) {
             const int k = c0 + tid;
-            const bool valid = tid < CHUNK && k < wu;   // the first CHUNK threads hold the chunk
+            const bool valid = k < wu;
             int x = 0, y = 0;
             bool blocked = !valid;
             if (valid) {
@@ -1247,17 +1343,22 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
             // in rank order at cx / cy [0, mu)
             {
                 const unsigned long long free_bits = __ballot(!blocked);
-                if (lane == 0 && wv < CHUNK / 64) sm.und[wv] = free_bits;
+                if (lane == 0) sm.und[wv] = free_bits;
             }
             __syncthreads();
+            const int most = nt == 0 && spaced ? CHUNK / 2 : CHUNK;
             int mu = 0, at = 0;
+            used = 0;
 #pragma unroll
-            for (int w = 0; w < CHUNK / 64; ++w) {
+            for (int w = 0; w < SBLOCK / 64; ++w) {
                 const int c = __popcll(sm.und[w]);
-                mu += c;
-                at += w < wv ? c : 0;
+                if (used == 64 * w && mu + c <= most) {
+                    at = w < wv ? mu + c : at;
+                    mu += c;
+                    used += 64;
+                }
             }
-            if (!blocked) {
+            if (!blocked && 64 * wv < used) {
                 at += __popcll(sm.und[wv] & ((1ull << lane) - 1));
                 sm.cxy[at] = (uint32_t)x | ((uint32_t)y << 16);
             }
@@ -1267,8 +1368,11 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
             // of 64: the triangle's 64 x 64 blocks (row group g, column group
             // h <= g) are dealt to the wavefronts in turn, a lane per row.
             // Positions are int16 pairs (coordinates < 32768): one packed
-            // subtract and one 16-bit dot product give dx^2 + dy^2 exactly
-            // (at most 2 * 32767^2 < 2^31).
+            // subtract and one 16-bit dot product give dx^2 + dy^2 - min_dist^2
+            // exactly (the squares are at most 2 * 32767^2 < 2^31), whose sign
+            // a funnel shift collects: three instructions a pair.  Entries of
+            // cxy past mu in a row group's columns are masked off by the rows
+            // that read them (columns h < g are full) or by the diagonal.
             if (spaced) {
                 const int ng = (mu + 63) >> 6;
                 const int nblk = ng * (ng + 1) / 2;
@@ -1280,20 +1384,25 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
                     const int t = 64 * g + lane;
                     if (t < mu) {
                         const s16x2 pt = __builtin_bit_cast(s16x2, sm.cxy[t]);
-                        const int u_end = h < g ? 64 : lane;    // columns 64 h + [0, u_end)
-                        unsigned long long mw = 0;
-                        for (int i0 = 0; i0 < u_end; i0 += 8) {
-                            const uint4 a = p4[(64 * h + i0) / 4], b = p4[(64 * h + i0) / 4 + 1];
-                            const uint32_t pu[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-                            uint32_t bits = 0;
+                        uint32_t bits[2];
 #pragma unroll
-                            for (int i = 0; i < 8; ++i) {
-                                const s16x2 d = pt - __builtin_bit_cast(s16x2, pu[i]);
-                                const int dd = __builtin_amdgcn_sdot2(d, d, 0, false);
-                                bits |= (uint32_t)(dd < md2 && i0 + i < u_end) << i;
+                        for (int half = 0; half < 2; ++half) {
+                            uint32_t b = 0;
+#pragma unroll
+                            for (int i0 = 28; i0 >= 0; i0 -= 4) {
+                                const uint4 a = p4[(64 * h + 32 * half + i0) / 4];
+                                const uint32_t pu[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+                                for (int i = 3; i >= 0; --i) {
+                                    const s16x2 d = pt - __builtin_bit_cast(s16x2, pu[i]);
+                                    // the sign of dx^2 + dy^2 - min_dist^2 moves in from the right
+                                    b = __builtin_amdgcn_alignbit(b, (uint32_t)__builtin_amdgcn_sdot2(d, d, -md2, false), 31);
+                                }
                             }
-                            mw |= (unsigned long long)bits << i0;
+                            bits[half] = b;
                         }
+                        unsigned long long mw = ((unsigned long long)bits[1] << 32) | bits[0];
+                        if (h == g) mw &= (1ull << lane) - 1;   // (only the better ones)
                         sm.cmask[t][h] = mw;
                     }
                 }
@@ -1347,7 +1456,7 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
                 if (w < wv) before += __popcll(sw);
                 else if (w == wv) before += __popcll(sw & ((1ull << lane) - 1));
             }
-            const bool mine = tid < mu && ((sm.sel[wv] >> lane) & 1ull);
+            const bool mine = tid < mu && ((sm.sel[wv] >> lane) & 1ull);   // (mu <= CHUNK)
             const int pos = nt + before;
             if (mine && pos < max_corners) {
                 const uint32_t pm = sm.cxy[tid];
