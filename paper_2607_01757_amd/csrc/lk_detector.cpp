@@ -47,21 +47,24 @@ lk_result detector_enqueue(lk_detector *det, std::vector<GfttJob> &jobs, const l
         return fail(LK_ERR_INVALID_ARG, "%d frames exceed the detector's %d", n_frames, det->max_frames);
     if (n_frames == 0) return LK_SUCCESS;
     int64_t pixels = 0;
+    bool general = false;
     for (int f = 0; f < n_frames; ++f) {
         const GfttJob &J = jobs[f];
         if (J.w < 3 || J.h < 3 || J.w > 32768 || J.h > 32768)
             return fail(LK_ERR_INVALID_ARG, "frame %d: size %dx%d not in [3, 32768]^2", f, J.w, J.h);
         if (J.pitch < J.w) return fail(LK_ERR_INVALID_ARG, "frame %d: pitch < width", f);
+        general |= J.response != nullptr || (int64_t)J.pitch * J.h > INT32_MAX;
         pixels += (int64_t)J.w * J.h;
     }
     long long tiles = 0;
     int64_t keep_words = 0;
     int tw = 0, th = 0;
-    gftt_tile_shape(p->radius, pixels, &tw, &th);
+    gftt_tile_shape(p->radius, general, pixels, &tw, &th);
+    const int lead = gftt_pairs(p->radius, general) ? 1 : 0;     // columns of the first strip left of the frame
     pixels = 0;
     for (int f = 0; f < n_frames; ++f) {
         GfttJob &J = jobs[f];
-        J.tiles_x = (J.w + tw - 1) / tw;
+        J.tiles_x = (J.w + lead + tw - 1) / tw;
         J.tile_begin = (int32_t)tiles;
         J.peaks = det->d_peaks + pixels;
         J.n_peaks = det->d_counts + 2 * f;
@@ -97,7 +100,7 @@ lk_result detector_enqueue(lk_detector *det, std::vector<GfttJob> &jobs, const l
     if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(detector jobs)");
     e = launch_gftt(static_cast<const GfttJob *>(slot->dev),
                     reinterpret_cast<const int32_t *>(static_cast<const char *>(slot->dev) + jbytes), n_frames,
-                    (int)tiles, th, p->radius, p->border, p->quality, p->min_dist, p->max_corners, s);
+                    (int)tiles, th, p->radius, general, p->border, p->quality, p->min_dist, p->max_corners, s);
     (void)hipEventRecord(slot->done, s);
     return e == hipSuccess ? LK_SUCCESS : hip_fail(e, "detector launch");
 }

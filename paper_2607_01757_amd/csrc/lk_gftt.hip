@@ -10,7 +10,9 @@
 //                  counters (a fill kernel, safe under graph capture);
 //   k_gftt_peaks   the response, its 3x3 local maxima with R > 0 appended to
 //                  the frame's peak list, the frame maximum raised with one
-//                  atomic per workgroup: block radius 0 and 1 walk 60x32
+//                  atomic per workgroup: block radius 1 without a response
+//                  map walks strips of 124 columns, two to a lane
+//                  (k_gftt_peaks_pair), radius 0 and 1 with a map 60x32
 //                  strips (60x64 in large calls) with one wavefront each
 //                  (k_gftt_peaks_strip), radius 2 and 3 stage 64x16 tiles
 //                  in LDS;
@@ -51,6 +53,22 @@ __device__ __forceinline__ int reflect101(int i, int n)
         if (i >= n) i = 2 * (n - 1) - i;
     }
     return i;
+}
+
+// One entry of a peak or candidate list, stored whole (16 bytes: a partly
+// written memory sector costs a read of the rest).
+__device__ __forceinline__ void put_peak(GfttPeak *list, uint32_t at, unsigned long long rbits, uint32_t idx)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    *(__attribute__((address_space(1))) u32x4 *)(list + at) = u32x4{(uint32_t)rbits, (uint32_t)(rbits >> 32), idx, 0u};
+}
+
+// A pointer read from a job, known to be device memory: its accesses do not
+// count as LDS accesses (a flat access in flight holds up every LDS wait).
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T *as_global(T *p)
+{
+    return (__attribute__((address_space(1))) T *)p;
 }
 
 // Correctly rounded square root of x, for x = 0 or x >= 1 (the discriminant
@@ -301,17 +319,25 @@ __device__ __forceinline__ double max_r(double a, double b)
     return m;
 }
 
+// from_left and from_right of a response
+__device__ __forceinline__ double double_from_left(double v)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    return __longlong_as_double((long long)(((unsigned long long)(uint32_t)from_left((int32_t)(uint32_t)(u >> 32)) << 32) |
+                                            (uint32_t)from_left((int32_t)(uint32_t)u)));
+}
+__device__ __forceinline__ double double_from_right(double v)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    return __longlong_as_double((long long)(((unsigned long long)(uint32_t)from_right((int32_t)(uint32_t)(u >> 32)) << 32) |
+                                            (uint32_t)from_right((int32_t)(uint32_t)u)));
+}
+
 // max of a lane's response and those of its two neighbours (0 at the end
 // lanes, whose maxima are not used)
 __device__ __forceinline__ double max3_lanes(double v)
 {
-    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-    const int32_t lo = (int32_t)(uint32_t)u, hi = (int32_t)(uint32_t)(u >> 32);
-    const double l = __longlong_as_double((long long)(((unsigned long long)(uint32_t)from_left(hi) << 32) |
-                                                       (uint32_t)from_left(lo)));
-    const double r = __longlong_as_double((long long)(((unsigned long long)(uint32_t)from_right(hi) << 32) |
-                                                       (uint32_t)from_right(lo)));
-    return max_r(v, max_r(l, r));
+    return max_r(v, max_r(double_from_left(v), double_from_right(v)));
 }
 
 template <int R, int SH>
@@ -534,6 +560,330 @@ __global__ __launch_bounds__(64 * kStripWaves) void k_gftt_peaks_strip(const Gft
         }
         if (lane == 0 && mb) atomicMax(J.max_bits, mb);
     }
+}
+
+// ---- peaks alone, block radius 1: two columns per lane -----------------------
+//
+// Without a response map only the local maxima need binary64.  This walk
+// brackets every response between two float32 bounds (twice the response: lo <=
+// (a + c) - sqrt((a - c)^2 + 4 b^2) <= hi), keeps the pixels whose upper bound
+// reaches the lower bounds of their 3x3 block, and evaluates the exact response
+// of those alone, 64 at a time.  A pixel whose lower bound reaches its
+// neighbours' upper bounds is a peak for certain; where the bounds leave a pair
+// open (plateaus, repeated patterns) the row takes the exact responses of its
+// block.  Pixels below quality times a maximum already known are dropped: they
+// are below the final threshold too.  The peaks the strip walk above finds and
+// these differ in such pixels only, which the compaction drops.
+//
+// Bounds: a, b, c are exact integers below 2^28.  With u = 2^-24 the conversions
+// and products leave (a - c)^2 + 4 b^2 within 4 u, its square root (1 ulp
+// instruction) within 4 u of a value at most a + c, the conversion of a + c and
+// the last rounding within u each: 6 u (a + c) in all, and 8 u is taken.
+//
+// Lane i owns columns c0 = xo - 2 + 2 i and c0 + 1 (xo: the strip's first
+// output column), as the halves of packed 16-bit registers: every gradient fits
+// 16 bits.  The frame is read with reflect-101 samples, so a gradient outside
+// the frame comes out as its mirror image with the component across that edge
+// negated: only the product gx gy changes sign, and strips at an edge undo that.
+// Lanes 1 .. 62 produce the strip's 124 columns.
+//
+// Rows are read by the lanes themselves, three ahead, not staged: the strip
+// needs no LDS but its candidates, and four wavefronts to a SIMD hide what is
+// left of the latency (staged through LDS, two: 177 us for the 60 Mpx below).
+//
+// VALU issue bounds large calls, a row's latency the small ones.  About 105
+// instruction slots a row and 124 pixels against 82 a row and 60 pixels of the
+// one-column binary64 walk: 64 mixed frames (60 Mpx) 206 us before, 124 us now;
+// one 752x480 frame 19.4 us before, 11 us now.
+
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ s16x2 as_s16x2(uint32_t v) { return __builtin_bit_cast(s16x2, v); }
+__device__ __forceinline__ uint32_t as_u32(s16x2 v) { return __builtin_bit_cast(uint32_t, v); }
+
+// x.lo * y.lo + c and x.hi * y.hi + c (signed 16-bit halves, exact)
+__device__ __forceinline__ int32_t mad_lo(s16x2 x, s16x2 y, int32_t c)
+{
+    int32_t r;
+    asm("v_mad_i32_i16 %0, %1, %2, %3" : "=v"(r) : "v"(as_u32(x)), "v"(as_u32(y)), "v"(c));
+    return r;
+}
+__device__ __forceinline__ int32_t mad_hi(s16x2 x, s16x2 y, int32_t c)
+{
+    int32_t r;
+    asm("v_mad_i32_i16 %0, %1, %2, %3 op_sel:[1,1,0,0]" : "=v"(r) : "v"(as_u32(x)), "v"(as_u32(y)), "v"(c));
+    return r;
+}
+
+// The bounds are compared as signed integers (the bits of a float order like
+// the float, except among negative ones): a candidate's upper bound is above
+// 0, so a maximum taken over negative bounds alone decides nothing, and the
+// integer maximum takes a neighbour lane's value in the same instruction.
+__device__ __forceinline__ int32_t bits_of(float v) { return __builtin_bit_cast(int32_t, v); }
+
+constexpr int kPairBatch = 384;                // candidates resolved at a time
+constexpr int kPairBuf = kPairBatch + 128;     // ... and the row of two columns that completes them
+
+__global__ __launch_bounds__(64) void k_gftt_peaks_pair(const GfttJob *__restrict__ jobs,
+                                                        const int32_t *__restrict__ tile_job, int tile_h, int border,
+                                                        float quality)
+{
+    __shared__ int4 s_buf[kPairBuf];                            // a, b, c, raster index and flag
+    const int lane = threadIdx.x;
+    const int tile = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x));
+    const GfttJob J = jobs[__builtin_amdgcn_readfirstlane(tile_job[tile])];
+    const int t = tile - J.tile_begin;
+    const int W = J.w, H = J.h;
+    const int xo = (t % J.tiles_x) * kGfttPairW - 1;            // (its first column is -1 in the first strip)
+    const int y0 = (t / J.tiles_x) * tile_h, ye = min(y0 + tile_h, H);          // output rows y0 .. ye-1
+    const int sy0 = y0 - 3;                                     // row 0 of the walk
+    // twice a response the frame has (0 at first); a stale value is a smaller one
+    const unsigned long long seen = __hip_atomic_load(as_global(J.max_bits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t *>(J.img), (short)0, J.pitch * H, 0x00020000);
+    const int c0 = xo - 2 + 2 * lane;                           // this lane's columns c0 and c0 + 1
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+    using S2 = std::integral_constant<int, 2>;
+    double vmax = 0.0;
+    uint32_t nbuf = 0;                                          // candidates in s_buf (wave-uniform)
+    // The buffer's candidates: their exact responses, 64 at a time and in place,
+    // then the peaks to one range of the list (one atomic: the counter is the
+    // frame's, and atomics on a counter's line take turns: with one for every 64
+    // candidates the mixed 64-frame walk took 194 us, with one for 384 162 us).
+    auto resolve = [&]() {
+        uint32_t n = 0;
+        __builtin_amdgcn_wave_barrier();                        // entries of the other lanes
+        for (uint32_t k = lane; k < nbuf; k += 64) {
+            const int4 e = s_buf[k];
+            const double r = min_eig(e.x, e.y, e.z);
+            vmax = max_r(vmax, r);
+            const bool peak = r > 0.0 && e.w >= 0;
+            const unsigned long long rb = (unsigned long long)__double_as_longlong(peak ? r : 0.0);
+            n += peak ? 1u : 0u;
+            s_buf[k] = make_int4((int)(uint32_t)rb, (int)(uint32_t)(rb >> 32), e.w, 0);
+        }
+        // places: the lanes' counts, one after the other
+        uint32_t at = n;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t v = __shfl_up(at, o, 64);
+            if (lane >= o) at += v;
+        }
+        const uint32_t all = __builtin_amdgcn_readlane(at, 63);
+        at -= n;
+        uint32_t base = 0;
+        if (lane == 0 && all)
+            base = (uint32_t)__hip_atomic_fetch_add(as_global(J.n_peaks), (int)all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        at += __builtin_amdgcn_readfirstlane(base);
+        for (uint32_t k = lane; k < nbuf; k += 64) {
+            const int4 e = s_buf[k];
+            if (e.x | e.y) {
+                put_peak(J.peaks, at, (unsigned long long)(uint32_t)e.y << 32 | (uint32_t)e.x, (uint32_t)e.z);
+                ++at;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        nbuf = 0;
+    };
+    auto walk = [&](auto edge_tag) {
+        // EDGE: the strip reaches past the frame (columns or rows)
+        constexpr bool EDGE = decltype(edge_tag)::value;
+        const bool in0 = !EDGE || (c0 >= 0 && c0 < W), in1 = !EDGE || (c0 + 1 >= 0 && c0 + 1 < W);
+        const s16x2 flip = {(short)(in0 ? 1 : -1), (short)(in1 ? 1 : -1)};
+        const bool out_lane = lane >= 1 && lane <= 62;
+        const bool o0 = out_lane && in0, o1 = out_lane && in1;
+        const uint32_t e0 = c0 >= border && c0 < W - border ? 0u : 0x80000000u;           // not a peak: the border
+        const uint32_t e1 = c0 + 1 >= border && c0 + 1 < W - border ? 0u : 0x80000000u;
+        constexpr float kLo = 1.0f - 0x1p-21f, kHi = 1.0f + 0x1p-21f;
+        constexpr int32_t kOut = INT32_MIN;                     // below every bound
+        const float q = quality * (1.0f - 0x1p-20f);            // (the host caps quality at 1)
+        // the largest lower bound so far
+        int32_t top = bits_of((float)(2.0 * __longlong_as_double((long long)seen)) * (1.0f - 0x1p-20f));
+        s16x2 hd[3], hs[3];                                     // differences and sums of three rows
+        int32_t pa[3][2], pb[3][2], pc[3][2];                   // horizontal sums of three gradient rows
+        int32_t ra[3][2], rb[3][2], rc[3][2];                   // block sums of three response rows
+        int32_t lo[3][2], hi[3][2];                             // bounds of three response rows
+        int32_t ml[3][2], mh[3][2], sh[3][2];                   // row maxima of lo, of hi, and of hi beside the column
+        // Rows come straight from memory, three ahead of their use: the four
+        // bytes at columns c0 - 1 .. c0 + 2 from one 8-byte load at the 4-byte
+        // aligned offset at or below them, or (EDGE) byte by byte at the
+        // reflect-101 columns.  The row of a load is a scalar offset.
+        uint32_t raw[3][EDGE ? 4 : 2];
+        int col[EDGE ? 4 : 1];
+        if constexpr (EDGE) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) col[k] = reflect1(min(max(c0 - 1 + k, -2), W + 1), W);
+        } else {
+            col[0] = (c0 - 1) & ~3;
+        }
+        const uint32_t shift = (uint32_t)((c0 - 1) & 3) * 8u;
+        auto load_row = [&](auto slot, int j) {
+            constexpr int Q = decltype(slot)::value;
+            const int so = reflect1(min(max(sy0 + j, -2), H + 1), H) * J.pitch;
+            if constexpr (EDGE) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) raw[Q][k] = __builtin_amdgcn_raw_buffer_load_b8(rs, col[k], so, 0);
+            } else {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, col[0], so, 0);
+                raw[Q][0] = v[0];
+                raw[Q][1] = v[1];
+            }
+        };
+        // row j (in raw slot Q); row j + 3 is loaded in its place
+        auto row_taps = [&](auto slot, int j, s16x2 &d, s16x2 &s) {
+            constexpr int Q = decltype(slot)::value;
+            s16x2 l, c, r;
+            if constexpr (EDGE) {
+                l = as_s16x2(raw[Q][0] | raw[Q][1] << 16);
+                c = as_s16x2(raw[Q][1] | raw[Q][2] << 16);
+                r = as_s16x2(raw[Q][2] | raw[Q][3] << 16);
+            } else {
+                const uint32_t v = __builtin_amdgcn_alignbit(raw[Q][1], raw[Q][0], shift);
+                l = as_s16x2(__builtin_amdgcn_perm(0u, v, 0x0c010c00u));
+                c = as_s16x2(__builtin_amdgcn_perm(0u, v, 0x0c020c01u));
+                r = as_s16x2(__builtin_amdgcn_perm(0u, v, 0x0c030c02u));
+            }
+            load_row(slot, j + 3);
+            d = r - l;
+            s = (s16x2)3 * (l + r) + (s16x2)10 * c;
+        };
+        // gradient row Yg (rows in slots O, O + 1, O + 2 mod 3) into
+        // product slot O + 2
+        auto grad_row = [&](auto o_slot, int Yg) {
+            constexpr int O = decltype(o_slot)::value, M = (O + 1) % 3, N = (O + 2) % 3;
+            row_taps(std::integral_constant<int, (O + 1) % 3>{}, Yg + 1 - sy0, hd[N], hs[N]);
+            const s16x2 gx = (s16x2)3 * (hd[O] + hd[N]) + (s16x2)10 * hd[M];
+            const s16x2 gy = hs[N] - hs[O];
+            s16x2 gf = gx;                                      // gx with the signs of the product gx gy undone
+            if constexpr (EDGE) {
+                const s16x2 f = Yg < 0 || Yg >= H ? -flip : flip;
+                gf = gx * f;
+            }
+            // the products of columns c0 - 1 and c0 + 2, from the neighbours
+            auto beside = [](s16x2 g) {
+                return as_s16x2(__builtin_amdgcn_alignbit((uint32_t)from_right((int32_t)as_u32(g)),
+                                                          (uint32_t)from_left((int32_t)as_u32(g)), 16));
+            };
+            const s16x2 bx = beside(gx), by = beside(gy), bf = EDGE ? beside(gf) : bx;
+            const int32_t xx = __builtin_amdgcn_sdot2(gx, gx, 0, false);
+            const int32_t xy = __builtin_amdgcn_sdot2(gf, gy, 0, false);
+            const int32_t yy = __builtin_amdgcn_sdot2(gy, gy, 0, false);
+            pa[N][0] = mad_lo(bx, bx, xx);
+            pa[N][1] = mad_hi(bx, bx, xx);
+            pb[N][0] = mad_lo(bf, by, xy);
+            pb[N][1] = mad_hi(bf, by, xy);
+            pc[N][0] = mad_lo(by, by, yy);
+            pc[N][1] = mad_hi(by, by, yy);
+        };
+        load_row(S0{}, 0);
+        load_row(S1{}, 1);
+        load_row(S2{}, 2);
+        row_taps(S0{}, 0, hd[1], hs[1]);
+        row_taps(S1{}, 1, hd[2], hs[2]);
+        grad_row(S1{}, y0 - 2);                                 // into product slot 0
+        grad_row(S2{}, y0 - 1);                                 // slot 1
+        // Response row Yr into slot Ws; with `out` the peaks of row Yr - 1
+        // (slot Ps), whose 3x3 blocks are complete.
+        auto step = [&](auto w_slot, auto p_slot, int Yr, bool out) {
+            constexpr int Ws = decltype(w_slot)::value, Ps = decltype(p_slot)::value;
+            grad_row(w_slot, Yr + 1);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                ra[Ws][k] = pa[0][k] + pa[1][k] + pa[2][k];
+                rb[Ws][k] = pb[0][k] + pb[1][k] + pb[2][k];
+                rc[Ws][k] = pc[0][k] + pc[1][k] + pc[2][k];
+                const float tr = (float)(ra[Ws][k] + rc[Ws][k]), df = (float)(ra[Ws][k] - rc[Ws][k]);
+                const float of = (float)rb[Ws][k];
+                const float root = __builtin_amdgcn_sqrtf(fmaf(4.0f, of * of, df * df));
+                lo[Ws][k] = bits_of(fmaf(tr, kLo, -root));
+                hi[Ws][k] = bits_of(fmaf(tr, kHi, -root));
+                if constexpr (EDGE)
+                    if (!(k ? in1 : in0) || Yr < 0 || Yr >= H) lo[Ws][k] = hi[Ws][k] = kOut;
+            }
+            {
+                const int32_t m = max(lo[Ws][0], lo[Ws][1]);
+                ml[Ws][0] = max(from_left(lo[Ws][1]), m);
+                ml[Ws][1] = max(from_right(lo[Ws][0]), m);
+                sh[Ws][0] = max(from_left(hi[Ws][1]), hi[Ws][1]);
+                sh[Ws][1] = max(from_right(hi[Ws][0]), hi[Ws][0]);
+                mh[Ws][0] = max(sh[Ws][0], hi[Ws][0]);
+                mh[Ws][1] = max(sh[Ws][1], hi[Ws][1]);
+            }
+            if (out) {
+                constexpr int Os = 3 - Ws - Ps;                 // row Yr - 2
+                const int Yo = Yr - 1;
+                top = max(top, max(lo[Ps][0], lo[Ps][1]));
+                const int32_t cut = bits_of(q * __builtin_bit_cast(float, top));
+                // (conditions joined without branches: the walk is short of
+                // wavefronts to hide them behind)
+                bool c0k = o0 & (hi[Ps][0] >= max(ml[0][0], max(ml[1][0], ml[2][0]))) & (hi[Ps][0] > cut);
+                bool c1k = o1 & (hi[Ps][1] >= max(ml[0][1], max(ml[1][1], ml[2][1]))) & (hi[Ps][1] > cut);
+                const bool open = (c0k & (lo[Ps][0] < max(mh[Os][0], max(sh[Ps][0], mh[Ws][0])))) |
+                                  (c1k & (lo[Ps][1] < max(mh[Os][1], max(sh[Ps][1], mh[Ws][1]))));
+                if (__builtin_expect(__ballot(open) != 0, 0)) {
+                    // exact responses of the three rows
+                    double v[3][2], m3[3][2];
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) {
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            v[j][k] = min_eig(ra[j][k], rb[j][k], rc[j][k]);
+                            if constexpr (EDGE) {
+                                const int Y = j == Ws ? Yr : (j == Ps ? Yo : Yr - 2);
+                                if (!(k ? in1 : in0) || Y < 0 || Y >= H) v[j][k] = -__builtin_inf();
+                            }
+                        }
+                        const double m = max_r(v[j][0], v[j][1]);
+                        m3[j][0] = max_r(m, double_from_left(v[j][1]));
+                        m3[j][1] = max_r(m, double_from_right(v[j][0]));
+                    }
+                    c0k = c0k && v[Ps][0] == max_r(m3[0][0], max_r(m3[1][0], m3[2][0]));
+                    c1k = c1k && v[Ps][1] == max_r(m3[0][1], max_r(m3[1][1], m3[2][1]));
+                }
+                const unsigned long long b0 = __ballot(c0k), b1 = __ballot(c1k);
+                const uint32_t ey = Yo >= border && Yo < H - border ? 0u : 0x80000000u;
+                const uint32_t n0 = (uint32_t)__popcll(b0);
+                const uint32_t idx = (uint32_t)(Yo * W + c0);
+                if (c0k)
+                    s_buf[nbuf + __builtin_amdgcn_mbcnt_hi((uint32_t)(b0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b0, 0u))] =
+                        make_int4(ra[Ps][0], rb[Ps][0], rc[Ps][0], (int)(idx | ey | e0));
+                if (c1k)
+                    s_buf[nbuf + n0 + __builtin_amdgcn_mbcnt_hi((uint32_t)(b1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b1, 0u))] =
+                        make_int4(ra[Ps][1], rb[Ps][1], rc[Ps][1], (int)((idx + 1) | ey | e1));
+                nbuf += n0 + (uint32_t)__popcll(b1);
+                if (nbuf >= kPairBatch) resolve();
+            }
+        };
+        step(S0{}, S2{}, y0 - 1, false);                        // rows y0 - 1 and y0: no output yet
+        step(S1{}, S0{}, y0, false);
+        for (int Yr = y0 + 1;; Yr += 3) {                       // ye >= y0 + 1
+            step(S2{}, S1{}, Yr, true);
+            if (Yr + 1 > ye) break;
+            step(S0{}, S2{}, Yr + 1, true);
+            if (Yr + 2 > ye) break;
+            step(S1{}, S0{}, Yr + 2, true);
+            if (Yr + 3 > ye) break;
+        }
+    };
+    // 8-byte loads stay in their row; the gradients of the walk lie in the frame
+    const bool aligned = (J.pitch & 3) == 0 && (reinterpret_cast<uintptr_t>(J.img) & 3) == 0;
+    if (aligned && xo - 3 >= 0 && xo + 131 < W && y0 - 2 >= 0 && ye + 1 < H) walk(std::false_type{});
+    else walk(std::true_type{});
+    // the rest of the candidates, and the strip's maximum (one atomic)
+    if (nbuf) resolve();
+    unsigned long long mb = (unsigned long long)__double_as_longlong(vmax);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const unsigned long long other = __shfl_xor(mb, o, 64);
+        mb = other > mb ? other : mb;
+    }
+    // (a strip that began after others had ended looks again: most need no
+    // atomic then; the first ones all end at about one time, where the look only
+    // adds its latency: 4.3 Mpx 31 us without it, 41 us with)
+    if (lane == 0 && mb > seen &&
+        (seen == 0 || mb > __hip_atomic_load(as_global(J.max_bits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+        atomicMax(J.max_bits, mb);
 }
 
 // ---- threshold --------------------------------------------------------------
@@ -1498,7 +1848,8 @@ __global__ void k_gftt_reset(const GfttJob *__restrict__ jobs)
 }  // namespace
 
 hipError_t launch_gftt(const GfttJob *d_jobs, const int32_t *d_tile_job, int njobs, int total_tiles, int tile_h,
-                       int radius, int border, double quality, int min_dist, int max_corners, hipStream_t s)
+                       int radius, bool general, int border, double quality, int min_dist, int max_corners,
+                       hipStream_t s)
 {
     if (njobs <= 0) return hipSuccess;
     k_gftt_reset<<<njobs, 256, 0, s>>>(d_jobs);
@@ -1508,6 +1859,11 @@ hipError_t launch_gftt(const GfttJob *d_jobs, const int32_t *d_tile_job, int njo
     case 1: {
         const dim3 grid((total_tiles + kStripWaves - 1) / kStripWaves), block(64 * kStripWaves);
         const bool tall = tile_h == kGfttStripHTall;
+        if (gftt_pairs(radius, general)) {
+            const float q = (float)(quality < 1.0 ? quality : 1.0);
+            k_gftt_peaks_pair<<<total_tiles, 64, 0, s>>>(d_jobs, d_tile_job, tile_h, border, q);
+            break;
+        }
         if (radius == 0 && tall) k_gftt_peaks_strip<0, kGfttStripHTall><<<grid, block, 0, s>>>(d_jobs, d_tile_job, total_tiles, border);
         else if (radius == 0) k_gftt_peaks_strip<0, kGfttStripH><<<grid, block, 0, s>>>(d_jobs, d_tile_job, total_tiles, border);
         else if (tall) k_gftt_peaks_strip<1, kGfttStripHTall><<<grid, block, 0, s>>>(d_jobs, d_tile_job, total_tiles, border);

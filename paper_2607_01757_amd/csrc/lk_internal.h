@@ -170,12 +170,28 @@ constexpr int kGfttTileW = 64, kGfttTileH = 16;      // response tiles, block ra
 // and their extra halo rows cost.
 constexpr int kGfttStripW = 60, kGfttStripH = 32, kGfttStripHTall = 64;
 constexpr int64_t kGfttTallPixels = int64_t(8) << 20;
+// Block radius 1 takes the two-column walk (strips of 124 columns, the first
+// starting at column -1), which evaluates the exact response of local maxima
+// only and reads a frame with 32-bit offsets.  A frame with a response map, or
+// of 2 GiB and more, makes the detection `general`: the strips above.
+constexpr int kGfttPairW = 124;
+// Strip height of that walk: a strip pays six rows of halo and two atomics, so
+// strips grow as soon as the chip is full of them (frames of 752x480, us at
+// heights 8 / 16 / 32 / 64: 1 frame 11.9 / 12.2 / 18 / 32, 3 frames 21 / 17 / 20
+// / 32, 12 frames 91 / 33 / 33 / 36, 24 frames 181 / 72 / 35 / 45, 64 frames
+// 342 / 200 / 89 / 68).
+inline int gftt_pair_height(int64_t pixels)
+{
+    return pixels < (3 << 18) ? 8 : (pixels < (3 << 19) ? 16 : (pixels < (3 << 22) ? 32 : 64));
+}
+inline bool gftt_pairs(int r, bool general) { return r == 1 && !general; }
 // Response tile (or strip) of a detection with block radius r over `pixels`
 // level-0 pixels in all.
-inline void gftt_tile_shape(int r, int64_t pixels, int *tw, int *th)
+inline void gftt_tile_shape(int r, bool general, int64_t pixels, int *tw, int *th)
 {
-    *tw = r <= 1 ? kGfttStripW : kGfttTileW;
-    *th = r <= 1 ? (pixels >= kGfttTallPixels ? kGfttStripHTall : kGfttStripH) : kGfttTileH;
+    const bool tall = pixels >= kGfttTallPixels, pairs = gftt_pairs(r, general);
+    *tw = pairs ? kGfttPairW : (r <= 1 ? kGfttStripW : kGfttTileW);
+    *th = pairs ? gftt_pair_height(pixels) : (r <= 1 ? (tall ? kGfttStripHTall : kGfttStripH) : kGfttTileH);
 }
 constexpr int kGfttWindow = 2048;             // peaks sorted per selection window
 constexpr int kGfttMaxCorners = LK_GFTT_MAX_CORNERS;
@@ -234,7 +250,8 @@ hipError_t launch_track_persistent(const BatchItem *d_items, int n_items, int to
 // Detection of every frame in d_jobs (reset, peaks, compaction, bucket layout,
 // selection: five launches).
 hipError_t launch_gftt(const GfttJob *d_jobs, const int32_t *d_tile_job, int njobs, int total_tiles, int tile_h,
-                       int radius, int border, double quality, int min_dist, int max_corners, hipStream_t stream);
+                       int radius, bool general, int border, double quality, int min_dist, int max_corners,
+                       hipStream_t stream);
 // Track-pool lifecycle kernels (lk_pool_kernels.hip), one workgroup per stream.
 hipError_t launch_pool_carry(const PoolJob *d_jobs, int n, hipStream_t stream);
 hipError_t launch_pool_append(const PoolJob *d_jobs, int n, hipStream_t stream);
