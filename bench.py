@@ -253,7 +253,7 @@ def detect_traffic():
     fill of 2 KiB per frame, is left out)."""
     parts = [profiled_traffic(k, summary="profiles/hbm_counters_detect64.txt",
                               source="paper_2607_01757_amd/csrc/lk_gftt.hip")
-             for k in ("k_gftt_peaks_strip", "k_gftt_compact", "k_gftt_bucket", "k_gftt_select")]
+             for k in ("k_gftt_peaks_pair", "k_gftt_compact", "k_gftt_bucket", "k_gftt_select")]
     return None if any(v is None for v in parts) else sum(parts)
 
 
