@@ -55,11 +55,13 @@ __device__ __forceinline__ int reflect101(int i, int n)
     return i;
 }
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 // One entry of a peak or candidate list, stored whole (16 bytes: a partly
 // written memory sector costs a read of the rest).
 __device__ __forceinline__ void put_peak(GfttPeak *list, uint32_t at, unsigned long long rbits, uint32_t idx)
 {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     *(__attribute__((address_space(1))) u32x4 *)(list + at) = u32x4{(uint32_t)rbits, (uint32_t)(rbits >> 32), idx, 0u};
 }
 
@@ -69,6 +71,13 @@ template <class T>
 __device__ __forceinline__ __attribute__((address_space(1))) T *as_global(T *p)
 {
     return (__attribute__((address_space(1))) T *)p;
+}
+
+// sizeof(V) bytes of a frame at p, which is aligned to them
+template <class V>
+__device__ __forceinline__ V load_wide(const uint8_t *p)
+{
+    return *(const __attribute__((address_space(1))) V *)p;
 }
 
 // Correctly rounded square root of x, for x = 0 or x >= 1 (the discriminant
@@ -146,15 +155,14 @@ __global__ __launch_bounds__(BLOCK) void k_gftt_peaks(const GfttJob *__restrict_
     //    sample (only those at distance 1 are ever read)
     {
         const bool vec_ok = (J.pitch & 15) == 0 && (reinterpret_cast<uintptr_t>(J.img) & 15) == 0;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint8_t *>(J.img), (short)0, J.pitch * H, 0x00020000);
         for (int e = tid; e < S::IH * (S::IW / 16); e += BLOCK) {
             const int j = e / (S::IW / 16), c = e - j * (S::IW / 16);
             const int Y = reflect1(min(max(y0 - 2 - R + j, -2), H + 1), H);
             const int X0 = x0 - 16 + 16 * c;
             if (vec_ok && X0 >= 0 && X0 + 16 <= W) {
+                // (64-bit offsets: pitch * h may pass 2 GiB)
                 *reinterpret_cast<uint4 *>(&sm.img[j][16 * c]) =
-                    __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, Y * J.pitch + X0, 0, 0));
+                    __builtin_bit_cast(uint4, load_wide<u32x4>(J.img + (size_t)Y * J.pitch + X0));
             } else {
 #pragma unroll
                 for (int k = 0; k < 16; ++k) {
@@ -366,15 +374,13 @@ __global__ __launch_bounds__(64 * kStripWaves) void k_gftt_peaks_strip(const Gft
     //    distance 1 are ever read)
     {
         const bool vec_ok = (J.pitch & 7) == 0 && (reinterpret_cast<uintptr_t>(J.img) & 7) == 0;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint8_t *>(J.img), (short)0, J.pitch * H, 0x00020000);
         for (int e = lane; e < S::IH * (S::IW / 8); e += 64) {
             const int j = e / (S::IW / 8), c = e - j * (S::IW / 8);
             const int Y = reflect1(min(max(sy0 + j, -2), H + 1), H);
             const int X0 = sx0 + 8 * c;
             if (vec_ok && X0 >= 0 && X0 + 8 <= W) {
                 *reinterpret_cast<uint2 *>(&sm.img[j][8 * c]) =
-                    __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rs, Y * J.pitch + X0, 0, 0));
+                    __builtin_bit_cast(uint2, load_wide<u32x2>(J.img + (size_t)Y * J.pitch + X0));
             } else {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {

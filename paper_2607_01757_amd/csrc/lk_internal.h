@@ -173,7 +173,8 @@ constexpr int64_t kGfttTallPixels = int64_t(8) << 20;
 // Block radius 1 takes the two-column walk (strips of 124 columns, the first
 // starting at column -1), which evaluates the exact response of local maxima
 // only and reads a frame with 32-bit offsets.  A frame with a response map, or
-// of 2 GiB and more, makes the detection `general`: the strips above.
+// of 2 GiB and more, makes the detection `general`: the strips above (64-bit
+// offsets).
 constexpr int kGfttPairW = 124;
 // Strip height of that walk: a strip pays six rows of halo and two atomics, so
 // strips grow as soon as the chip is full of them (frames of 752x480, us at
