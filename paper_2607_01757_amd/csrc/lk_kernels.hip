@@ -1481,7 +1481,11 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
         pr.status = LK_LOST_OOB;
         return pr;                 // (every wavefront of the point)
     }
-    // the end of this wavefront's part of the pass, level l
+    // the end of this wavefront's part of the pass, level l.  (Every return of
+    // this function names `pr`: one that returned another object would keep the
+    // result out of the caller's registers, and both forms of the pass would
+    // spill or grow: 2 spilled registers in the one-wavefront kernel, 109
+    // registers instead of 69 in the float32 kernel by levels.)
     auto leave = [&](int l) {
         if constexpr (LV) {
             if (lc.lane0) baton[l] = Baton{pr.status, gx, gy, pr.ox, pr.oy, pr.fx, pr.fy, pr.res};
@@ -1492,7 +1496,6 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
             pr.fx = uniform_f(e.fx); pr.fy = uniform_f(e.fy);
             pr.res = uniform_f(e.res);
         }
-        return pr;
     };
     float T[R][CW], GX[R][CW], GY[R][CW];
     float dx = 0.0f, dy = 0.0f;
@@ -1574,10 +1577,13 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
             pr.status = LK_LOST_EIG;
             pr.ox = ldexpf((float)cix + (cfx + gx), l);
             pr.oy = ldexpf((float)ciy + (cfy + gy), l);
-            return leave(l);
+            leave(l);
         };
         if constexpr (!LV)
-            if (!textured) return lost_eig();
+            if (!textured) {
+                lost_eig();
+                return pr;
+            }
         const float rdet = __builtin_amdgcn_rcpf(det);      // 1 ulp
         const float lox = (float)(-h - cix), hix = (float)(LJ.w - 1 + h - cix);
         const float loy = (float)(-h - ciy), hiy = (float)(LJ.h - 1 + h - ciy);
@@ -1627,11 +1633,15 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
                 if (uniform_i(c.status) != LK_OK) {
                     pr.status = uniform_i(c.status);
                     pr.ox = uniform_f(c.ox); pr.oy = uniform_f(c.oy);
-                    return leave(l);
+                    leave(l);
+                    return pr;
                 }
                 gx = uniform_f(c.gx); gy = uniform_f(c.gy);
             }
-            if (!textured) return lost_eig();
+            if (!textured) {
+                lost_eig();
+                return pr;
+            }
         }
         // The taps of the first estimate are loaded before the iterations
         // (its integer part clamped to the level's range: an estimate outside
@@ -1710,13 +1720,17 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
             pr.ox = ldexpf((float)cix + ux, l);
             pr.oy = ldexpf((float)ciy + uy, l);
             if (iters && lc.lane0) iters[l] = k - 1;
-            return leave(l);
+            leave(l);
+            return pr;
         }
         if (iters && lc.lane0) iters[l] = k;
         if (l > 0) {
             gx = 2.0f * (gx + dx);
             gy = 2.0f * (gy + dy);
-            if constexpr (LV) return leave(l);
+            if constexpr (LV) {
+                leave(l);
+                return pr;
+            }
             continue;
         }
         if constexpr (G::R <= 7 && ST == LK_STORAGE_F32) {
@@ -1744,7 +1758,8 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
         load_lane_taps<G, K_U8>(PJ, bx - h + lc.c0, by - h + lc.r0, inside, jt);
         finish_level0<G>(lc, win, nw, T, jt, ux, uy, fux, fuy, cix, ciy, cfx, cfy, LJ, pr);
     }
-    return leave(0);
+    leave(0);
+    return pr;
 }
 
 // The forward-backward check of a point tracked by the forward pass f.
