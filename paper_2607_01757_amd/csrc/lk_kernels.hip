@@ -1598,8 +1598,12 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
         // the level's last row
         constexpr bool PAIR = ST == LK_STORAGE_F16 && G::CW == 1;
         TapRegion<G> region{INT_MIN / 2, INT_MIN / 2};     // (holds no window)
-        auto load_target = [&](int bx, int by) {
-            if constexpr (LV && ST == LK_STORAGE_F32)
+        // The level's first window may come from the region: its taps are new to
+        // the wavefront.  Those of later ones are mostly in the cache, and the
+        // same test in the iterations cost the points that take all 30 of them
+        // up to 8% of the launch (21x21 and smaller against an unrelated frame).
+        auto load_target = [&](int bx, int by, auto first) {
+            if constexpr (LV && ST == LK_STORAGE_F32 && decltype(first)::value)
                 if (region.holds(bx - h, by - h)) {
                     region.taps(lds, bx - h, by - h, lc, jt);
                     return;
@@ -1652,7 +1656,7 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
         // copy of every tap per level).
         int jbx = uniform_i(cix + (int)fminf(fmaxf(floorf(cfx + gx), lox), hix));
         int jby = uniform_i(ciy + (int)fminf(fmaxf(floorf(cfy + gy), loy), hiy));
-        load_target(jbx, jby);
+        load_target(jbx, jby, std::true_type{});
         // The cell [fbx, fbx + 1) x [fby, fby + 1) of the loaded taps (level
         // coordinates relative to c, exact small integers).  While an estimate
         // stays in it, its integer part is the loaded one, and when the cell
@@ -1677,7 +1681,7 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
                 const float fux = floorf(ux), fuy = floorf(uy);
                 const int bx = uniform_i(cix + (int)fux), by = uniform_i(ciy + (int)fuy);
                 if (bx != jbx || by != jby) {
-                    load_target(bx, by);
+                    load_target(bx, by, std::false_type{});
                     jbx = bx; jby = by;
                 }
                 fbx = fux; fby = fuy;
@@ -1742,7 +1746,7 @@ __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, flo
             const float fux = fminf(fmaxf(floorf(ux), (float)(-cix - h - 2)), (float)(LJ.w + h + 2 - cix));
             const float fuy = fminf(fmaxf(floorf(uy), (float)(-ciy - h - 2)), (float)(LJ.h + h + 2 - ciy));
             const int bx = uniform_i(cix + (int)fux), by = uniform_i(ciy + (int)fuy);
-            if (bx != jbx || by != jby) load_target(bx, by);
+            if (bx != jbx || by != jby) load_target(bx, by, std::false_type{});
             finish_level0<G>(lc, win, nw, T, jt, ux, uy, fux, fuy, cix, ciy, cfx, cfy, LJ, pr);
         }
     }
@@ -2033,19 +2037,26 @@ inline unsigned blocks_for(long waves) { return (unsigned)((waves + G::WPB - 1) 
 // Whether a launch of n keypoints takes a wavefront per level: when all their
 // workgroups are resident at once.  Up to there the side-by-side templates
 // shorten the launch; past it the waiting wavefronts hold room that a second
-// round of workgroups needs.  Measured (us, wavefront per level against one
-// wavefront per keypoint, back to back): 21x21, 3 levels, float32, no backward
-// pass: 9.4 / 12.5 at 150 keypoints, 12.0 / 15.0 at 1280 (the limit), 17.4 /
-// 15.6 at 1500; 4 levels with the backward pass 21 / 31 at 150, 28 / 37 at
-// 1000, 42 / 38 at 1280 (limit 1024); 31x31, 4 levels, backward pass, binary16
-// 26 / 37 at 150, 34 / 46 at 768 (the limit), 53 / 46 at 1000; 31x31, float32,
-// forward only 16 / 33 at 150, 18 / 35 at 500, 32 / 37 at 600 (limit 512).
+// round of workgroups needs.  Three wavefronts leave out one SIMD of the four,
+// so with 3 levels the last slot of a CU is not counted on.  Measured (us,
+// wavefront per level against one wavefront per keypoint, back to back, no
+// backward pass; `lost`: the target is an unrelated frame and the points take
+// every iteration, which leaves nothing to gain): 21x21 float32, 3 levels: 11.0
+// / 14.4 at 100 keypoints, 14.8 / 18.3 at 1280 (the limit; lost 72.1 / 72.8);
+// 4 levels 12.4 / 19.0 at 256, 14.8 / 21.2 at 1024 (the limit; lost 85.8 /
+// 87.4); 2 levels 14.0 / 13.9 at 2048 (the limit; lost 54.6 / 54.2); 21x21
+// binary16, 3 levels: 13.2 / 14.9 at 1024, 15.2 / 16.1 at 1792 (the limit; lost
+// 75.0 / 73.8), lost 80.0 / 74.9 at 2048; 31x31 binary16, 3 levels: 16.7 / 20.6
+// at 768 (the limit; lost 93.3 / 94.3), lost 110.5 / 95.4 at 1024; 31x31
+// float32, 4 levels: 17.4 / 34.1 at 256, 18.1 / 34.0 at 512 (the limit; lost
+// 108 / 121).  (256: the CUs of an MI355X.)
 constexpr int kCUs = 256;
 
 template <int ST, class G>
 inline bool use_level_waves(const TrackArgs &a)
 {
-    return a.levels >= 2 && a.levels <= kLevelWaves && a.n <= kCUs * (4 * kLevelOcc<ST, G> / a.levels);
+    const int slots = 4 * kLevelOcc<ST, G> - (a.levels == 3 ? 1 : 0);      // wavefronts of a CU
+    return a.levels >= 2 && a.levels <= kLevelWaves && a.n <= kCUs * (slots / a.levels);
 }
 
 template <int ST, class G>
