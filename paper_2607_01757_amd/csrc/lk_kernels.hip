@@ -1781,8 +1781,7 @@ __device__ void track_point(const PyrDesc &prev, const PyrDesc &next, const Trac
 {
     const LaneCfg lc = lane_cfg<G>(a.win, lane);
     const int L = a.levels;
-    // (scalar loads: no keypoint's wavefront but its own may write its entry)
-    const float px = as_constant(a.pts)[2 * idx], py = as_constant(a.pts)[2 * idx + 1];
+    const float px = uniform_f(a.pts[2 * idx]), py = uniform_f(a.pts[2 * idx + 1]);
     float gx = 0.0f, gy = 0.0f;
     if (a.use_guess) {
         gx = ldexpf(uniform_f(a.guess[2 * idx]) - px, -(L - 1));
@@ -1827,8 +1826,7 @@ __device__ __forceinline__ void track_point_levels(const PyrDesc &prev, const Py
 {
     const LaneCfg lc = lane_cfg<G>(a.win, lane);
     const int L = a.levels;
-    // (scalar loads: no keypoint's wavefront but its own may write its entry)
-    const float px = as_constant(a.pts)[2 * idx], py = as_constant(a.pts)[2 * idx + 1];
+    const float px = uniform_f(a.pts[2 * idx]), py = uniform_f(a.pts[2 * idx + 1]);
     float gx = 0.0f, gy = 0.0f;
     if (a.use_guess) {
         gx = ldexpf(uniform_f(a.guess[2 * idx]) - px, -(L - 1));
