@@ -2081,16 +2081,21 @@ hipError_t launch_track_st(const PyrDesc *prev, const PyrDesc *next, const Track
     }
 }
 
-// by_level: the launch may take a wavefront per level (no shape was asked for).
 template <int ST, class G>
-hipError_t launch_track_batched_g(const BatchItem *items, int n_items, const TrackArgs &a, hipStream_t s, bool by_level)
+hipError_t launch_track_batched_g(const BatchItem *items, int n_items, const TrackArgs &a, hipStream_t s)
 {
-    if (by_level && use_level_waves<ST, G>(a)) {
-        hipLaunchKernelGGL((k_track_batched_levels<ST, G>), dim3(a.n), dim3(a.levels * 64),
-                           a.levels * G::LDS * sizeof(float), s, items, n_items, a);
-        return hipGetLastError();
-    }
     hipLaunchKernelGGL((k_track_batched<ST, G>), dim3(blocks_for<G>(a.n)), dim3(G::WPB * 64), 0, s, items, n_items, a);
+    return hipGetLastError();
+}
+
+// The layout's default shape (no other was asked for): a wavefront per level
+// where use_level_waves says so.
+template <int ST, class G>
+hipError_t launch_track_batched_default(const BatchItem *items, int n_items, const TrackArgs &a, hipStream_t s)
+{
+    if (!use_level_waves<ST, G>(a)) return launch_track_batched_g<ST, G>(items, n_items, a, s);
+    hipLaunchKernelGGL((k_track_batched_levels<ST, G>), dim3(a.n), dim3(a.levels * 64),
+                       a.levels * G::LDS * sizeof(float), s, items, n_items, a);
     return hipGetLastError();
 }
 
@@ -2099,14 +2104,17 @@ hipError_t launch_track_batched_st(const BatchItem *items, int n_items, const Tr
 {
     switch (choose_layout(a.win)) {
     case LAYOUT_W21:
-        if (a.win != GeoW21X::WMAX) return wpg <= 1 ? launch_track_batched_g<ST, GeoW21>(items, n_items, a, s, wpg == 0)
-                                                     : hipErrorInvalidValue;
-        if (wpg == 2) return launch_track_batched_g<ST, GeoW21X2>(items, n_items, a, s, wpg == 0);
-        if (wpg == 4) return launch_track_batched_g<ST, GeoW21X4>(items, n_items, a, s, wpg == 0);
-        return wpg <= 1 ? launch_track_batched_g<ST, GeoW21X>(items, n_items, a, s, wpg == 0) : hipErrorInvalidValue;
+        if (a.win != GeoW21X::WMAX) {
+            if (wpg == 0) return launch_track_batched_default<ST, GeoW21>(items, n_items, a, s);
+            return wpg == 1 ? launch_track_batched_g<ST, GeoW21>(items, n_items, a, s) : hipErrorInvalidValue;
+        }
+        if (wpg == 0) return launch_track_batched_default<ST, GeoW21X>(items, n_items, a, s);
+        if (wpg == 2) return launch_track_batched_g<ST, GeoW21X2>(items, n_items, a, s);
+        if (wpg == 4) return launch_track_batched_g<ST, GeoW21X4>(items, n_items, a, s);
+        return wpg == 1 ? launch_track_batched_g<ST, GeoW21X>(items, n_items, a, s) : hipErrorInvalidValue;
     case LAYOUT_W31:
-        return wpg == 0 || wpg == GeoW31::WPB ? launch_track_batched_g<ST, GeoW31>(items, n_items, a, s, wpg == 0)
-                                               : hipErrorInvalidValue;
+        if (wpg == 0) return launch_track_batched_default<ST, GeoW31>(items, n_items, a, s);
+        return wpg == GeoW31::WPB ? launch_track_batched_g<ST, GeoW31>(items, n_items, a, s) : hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
 }

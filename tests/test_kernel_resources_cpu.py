@@ -39,3 +39,11 @@ def spills(kernels, pattern):
 @pytest.mark.parametrize("geo", ["ILi1ELi7ELi21ELi1ELi6ELb1E", "ILi1ELi7ELi21ELi1ELi4ELb0E", "ILi1ELi16ELi31ELi4ELi2ELb0E"])
 def test_tracker_does_not_spill(kernels, kernel, storage, geo):
     assert spills(kernels, r"\d%sILi%dENS0_3Geo%s" % (kernel, storage, geo)) == {}
+
+
+def test_no_level_kernel_without_a_launch(kernels):
+    """The launch by levels exists for the default shapes only: no kernel of it
+    is built for the 2 and 4 keypoints a workgroup that a program can ask for."""
+    names = [n for n in kernels if "k_track_batched_levels" in n]
+    assert len(names) == 6                     # three layouts, two storages
+    assert not [n for n in names if re.search(r"ILi1ELi7ELi21ELi[24]E", n)]
