@@ -216,7 +216,9 @@ lk_result lk_track_batched_noalloc(lk_context *ctx, const lk_pair *h_pairs, int3
  *     stealing from other XCDs when its own range is done);
  *   use_graph = 1: the whole step is recorded into a HIP graph at creation
  *     (and after lk_batch_tune) and replayed by lk_batch_run.
- *   waves_per_group (hardware dispatch): wavefronts per workgroup;
+ *   waves_per_group (hardware dispatch): wavefronts per workgroup (0: a small
+ *     step may take a workgroup per keypoint with one wavefront per pyramid
+ *     level; any other value keeps one wavefront per keypoint);
  *   chunk (persistent grid): keypoints per work fetch.
  * lk_batch_tune times every candidate shape on this batch (after about 20 ms
  * of untimed steps that bring the device to its steady clock; reps launches

@@ -291,10 +291,12 @@ lk_result lk_batch_tune(lk_batch *b, lk_stream stream, int32_t reps, lk_exec_con
     const int use_graph = b->cfg.use_graph;
     // candidates: hardware dispatch with every built workgroup size, and
     // persistent grids (half and full residency of the 5-wave build, fine
-    // and coarse work fetches)
+    // and coarse work fetches).  One wavefront a workgroup is the default
+    // shape unless that takes a wavefront per level.
+    const bool by_levels = track_batched_by_levels(b->args, b->storage);
     std::vector<lk_exec_config> cands;
-    for (int w : {0, 2, 4})
-        if (track_waves_supported(b->win, w)) cands.push_back({0, 0, 0, 0, w, 0});
+    for (int w : {0, 1, 2, 4})
+        if (track_waves_supported(b->win, w) && (w != 1 || by_levels)) cands.push_back({0, 0, 0, 0, w, 0});
     for (int bpc : {10, 20})
         for (int chunk : {8, 32}) cands.push_back({1, bpc, 0, chunk, 0, 0});
     hipEvent_t a, z;

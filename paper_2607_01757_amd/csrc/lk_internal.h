@@ -240,6 +240,8 @@ hipError_t launch_write_descs(const PyrDescWrite *d_w, int n, hipStream_t stream
 hipError_t launch_track_batched(const BatchItem *d_items, int n_items, int total_points,
                                 const TrackArgs &a, int storage, hipStream_t stream, int waves_per_group = 0);
 bool track_waves_supported(int win, int waves_per_group);
+// The default shape of that launch (a.n keypoints) takes a wavefront per level.
+bool track_batched_by_levels(const TrackArgs &a, int storage);
 // Persistent tracker grid: blocks_per_cu workgroups per compute unit, each
 // wavefront taking `chunk` keypoints per fetch; 8 work counters at
 // d_counters, kCounterStride ints apart (zeroed by the launch itself).

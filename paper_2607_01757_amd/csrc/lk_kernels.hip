@@ -2148,6 +2148,16 @@ hipError_t launch_downsample(const DownJob &job, hipStream_t stream)
     return hipGetLastError();
 }
 
+bool track_batched_by_levels(const TrackArgs &a, int storage)
+{
+    const bool f16 = storage == LK_STORAGE_F16;
+    switch (choose_layout(a.win)) {
+    case LAYOUT_W21: return f16 ? use_level_waves<LK_STORAGE_F16, GeoW21>(a) : use_level_waves<LK_STORAGE_F32, GeoW21>(a);
+    case LAYOUT_W31: return f16 ? use_level_waves<LK_STORAGE_F16, GeoW31>(a) : use_level_waves<LK_STORAGE_F32, GeoW31>(a);
+    default: return false;
+    }
+}
+
 hipError_t launch_downsample_batched(const DownJob *d_jobs, const int32_t *d_tile_job, int total_tiles,
                                      hipStream_t stream)
 {
