@@ -631,7 +631,7 @@ __device__ __forceinline__ int32_t bits_of(float v) { return __builtin_bit_cast(
 // on with the exact responses of every pixel.  An open row costs about twice a
 // row's slots more, exact responses a quarter more on every row.  Walk of 64
 // frames of 752x480 whose rows are open for 3 in 4 (isolated bright dots): 153 us
-// without, 89 us with it (the one-column walk 97); of low texture (1 in 4)
+// without, 92 us with it (the one-column walk 97); of low texture (1 in 4)
 // 109 / 92 (93).  Frames without open rows keep their times within 2%.
 constexpr int kPairOpen = 12;
 constexpr int kPairBatch = 384;                // candidates resolved at a time
