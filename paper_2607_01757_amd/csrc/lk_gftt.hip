@@ -1497,7 +1497,7 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
                 // longer: checks of 8 pixels, 752x480, 1000 corners at spacing
                 // 8, 683 us with full windows only, 877 with half ones, 673 so.)
                 const int passes = (d - lz) / 8;
-                if ((wn - (int)need) * (passes + 1) >= wn * passes) {
+                if (d <= 88 && (wn - (int)need) * (passes + 1) >= wn * passes) {
                     // without the digit the full window would end in
                     prefix = key_after_digit(prefix, d);
                     wn -= (int)need;

@@ -47,8 +47,10 @@ __host__ __device__ __forceinline__ Key key_with_digit(Key q, int p, uint32_t v)
     return Key{(unsigned long long)(t >> 64), (uint32_t)(t >> 32)};
 }
 
-// the least key above every key with q's leading p + 8 bits, 0 <= p < 96
-// (there is one: no key starts with as many ones)
+// the least key above every key with q's leading p + 8 bits, 0 <= p <= 88 (there
+// is one: no key starts with as many ones).  Past 88 the digit holds fewer than
+// 8 bits of the key and the result is q itself: such a digit names one key, so
+// a selection that asks for what lies above it has taken it whole before.
 __host__ __device__ __forceinline__ Key key_after_digit(Key q, int p)
 {
     const unsigned __int128 t = ((key_top(q) >> (120 - p)) + 1) << (120 - p);
