@@ -1412,6 +1412,11 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
     __syncthreads();
 
     while (nt < max_corners && remaining > 0) {
+        // (the thread's index anew: addresses formed of it outside the loop would
+        // be held through it, more than the registers take)
+        int tid = (int)threadIdx.x;
+        asm("" : "+v"(tid));
+        const int lane = tid & 63, wv = tid >> 6;
         // ---- the next window: the best min(CAPW, remaining) candidates,
         // ranks [consumed, consumed + wn) of the descending order
         const int consumed = np - remaining;
@@ -1763,17 +1768,19 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
             }
             __syncthreads();
             const int most = nt == 0 && spaced ? CHUNK / 2 : CHUNK;
-            int mu = 0, at = 0;
-            used = 0;
-#pragma unroll
-            for (int w = 0; w < SBLOCK / 64; ++w) {
-                const int c = __popcll(sm.und[w]);
-                if (used == 64 * w && mu + c <= most) {
-                    at = w < wv ? mu + c : at;
-                    mu += c;
-                    used += 64;
-                }
-            }
+            // (lane w of every wavefront counts wavefront w's, and the running sums
+            // up to `most` are the leading wavefronts'; the 16 masks in every
+            // lane would take 32 registers)
+            static_assert(SBLOCK / 64 == 16, "a wavefront's count in each lane of a row of 16");
+            uint32_t upto = lane < SBLOCK / 64 ? (uint32_t)__popcll(sm.und[lane & (SBLOCK / 64 - 1)]) : 0u;
+            upto += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)upto, 0x111, 0xF, 0xF, true);     // row_shr:1, 2, 4, 8
+            upto += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)upto, 0x112, 0xF, 0xF, true);
+            upto += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)upto, 0x114, 0xF, 0xF, true);
+            upto += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)upto, 0x118, 0xF, 0xF, true);
+            const int lead = __popcll(__ballot(lane < SBLOCK / 64 && (int)upto <= most));
+            used = 64 * lead;
+            const int mu = lead ? __builtin_amdgcn_readlane((int)upto, lead - 1) : 0;
+            int at = wv ? __builtin_amdgcn_readlane((int)upto, wv - 1) : 0;
             if (!blocked && 64 * wv < used) {
                 at += __popcll(sm.und[wv] & ((1ull << lane) - 1));
                 sm.cxy[at] = (uint32_t)x | ((uint32_t)y << 16);

@@ -41,6 +41,11 @@ def test_tracker_does_not_spill(kernels, kernel, storage, geo):
     assert spills(kernels, r"\d%sILi%dENS0_3Geo%s" % (kernel, storage, geo)) == {}
 
 
+@pytest.mark.parametrize("kernel", ["k_gftt_select", "k_gftt_peaks_pair", "k_gftt_compact", "k_gftt_bucket"])
+def test_detector_does_not_spill(kernels, kernel):
+    assert spills(kernels, r"\d" + kernel) == {}
+
+
 def test_no_level_kernel_without_a_launch(kernels):
     """The launch by levels exists for the default shapes only: no kernel of it
     is built for the 2 and 4 keypoints a workgroup that a program can ask for."""
