@@ -1271,6 +1271,7 @@ constexpr int SBLOCK = 1024;                  // threads of the selection workgr
 constexpr int CHUNK = 512;                    // unblocked candidates decided together, at most
 constexpr int STEPS = 2048;                   // steps of a window's range in the counting sort
 constexpr uint32_t STEP_KEYS = 32;            // keys of one step, at most, for that sort
+constexpr int kWindowCost = 4;                // a window's gathering, sort and decisions, in radix passes
 constexpr int KPT = 4;                        // keys per thread in flight in the list passes
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
@@ -1496,13 +1497,16 @@ __global__ __launch_bounds__(SBLOCK) void k_gftt_select(const GfttJob *__restric
                 if (whole) break;
                 // The window may end above the digit a full one would end in,
                 // if that costs less a key: `passes` so far for the smaller
-                // window against at least one more for the full one.  (With
-                // half a window accepted after any pass, plateaus, whose
-                // windows take ten passes over a long bucket, took up to 28%
-                // longer: checks of 8 pixels, 752x480, 1000 corners at spacing
-                // 8, 683 us with full windows only, 877 with half ones, 673 so.)
+                // window against at least one more for the full one, and for
+                // both kWindowCost passes' worth of gathering, sorting and
+                // deciding.  (Half a window accepted after any pass made plateaus,
+                // whose windows take ten passes over a long bucket, up to 28%
+                // slower than full windows only.  Checks of 8 pixels, 200
+                // corners, us with full windows, half ones, and this rule: 752
+                // wide 1284 / 1392 / 1236, 751 wide 1292 / 1398 / 1250; 1000
+                // corners at spacing 8 684 / 879 / 646.)
                 const int passes = (d - lz) / 8;
-                if (d <= 88 && (wn - (int)need) * (passes + 1) >= wn * passes) {
+                if (d <= 88 && (wn - (int)need) * (passes + kWindowCost + 1) >= wn * (passes + kWindowCost)) {
                     // without the digit the full window would end in
                     prefix = key_after_digit(prefix, d);
                     wn -= (int)need;
