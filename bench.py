@@ -877,12 +877,14 @@ def run_detect(args):
         assert np.array_equal(got, want), "detector differs from the oracle on frame %d" % i
     # algorithmic operations per pixel (radius 1): Scharr pair 16, tensor
     # products 3, separable 3x3 sums 12, two integer tensor combinations 2,
-    # NMS 8 compares (41 integer ops) + 10 binary64 ops (3 conversions, 3
-    # products, a sum, the square root, a difference, a halving).  CDNA4
-    # issues a binary64 VALU op at the rate of an int32 one: one op per lane
-    # per clock, 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3 T lane-ops/s
-    # (the fp32 vector peak / 4: no FMA pairs, no packed pairs)
-    ops = px * (41 + 10)
+    # NMS 8 compares: 41 integer operations.  The binary64 response (10 more)
+    # is not counted: the walk forms it for a few candidates in a hundred
+    # pixels only.  A share of the algorithm's operations, not the unit's
+    # utilisation: the walk packs two 16-bit operations into many of its
+    # instructions.  One op per lane per clock, 256 CUs x 4 SIMDs x 16 lanes x
+    # 2.4 GHz = 39.3 T lane-ops/s (the fp32 vector peak / 4: no FMA pairs, no
+    # packed pairs)
+    ops = px * 41
     peak_lane_ops = PEAK_FP32_TFLOPS / 4
     t = res["fresh"]["ms_per_step"] * 1e-3
     result = {

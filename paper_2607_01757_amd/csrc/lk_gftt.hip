@@ -28,11 +28,12 @@
 //                  96-bit rank key (R bits, then the complemented raster
 //                  index); they are sorted in LDS and accepted up to 512 at a
 //                  time against the corners taken so far and the occupied points.
-//                  Latency bounds it: one 752x480 frame 58.8 us with a bitonic
-//                  sort, chunks of 512 and windows of exactly 2048, 32.8 us with
+//                  Latency bounds it: one 752x480 frame 58 us with a bitonic
+//                  sort, chunks of 512 and windows of exactly 2048, 30 us with
 //                  the counting sort (-14), the half first chunk and wider checks
-//                  (-9), three instructions a pair (-3) and windows that end
-//                  where the digits allow; 64 mixed frames 104 -> 77 us.
+//                  (-9), three instructions a pair (-3), windows that may end
+//                  above a digit, and no spilled registers (-3); 64 mixed
+//                  frames 105 -> 71 us.
 //                  The acceptance within a chunk resolves the greedy rule
 //                  exactly (a candidate is taken iff no better candidate that
 //                  is taken lies too close).
@@ -577,9 +578,10 @@ __global__ __launch_bounds__(64 * kStripWaves) void k_gftt_peaks_strip(const Gft
 // of those alone, 64 at a time.  A pixel whose lower bound reaches its
 // neighbours' upper bounds is a peak for certain; where the bounds leave a pair
 // open (plateaus, repeated patterns) the row takes the exact responses of its
-// block.  Pixels below quality times a maximum already known are dropped: they
-// are below the final threshold too.  The peaks the strip walk above finds and
-// these differ in such pixels only, which the compaction drops.
+// block, and a strip with many such rows goes on with exact responses alone.
+// Pixels below quality times a maximum already known are dropped: they are below
+// the final threshold too.  The peaks the strip walk above finds and these
+// differ in such pixels only, which the compaction drops.
 //
 // Bounds: a, b, c are exact integers below 2^28.  With u = 2^-24 the conversions
 // and products leave (a - c)^2 + 4 b^2 within 4 u, its square root (1 ulp
@@ -595,12 +597,13 @@ __global__ __launch_bounds__(64 * kStripWaves) void k_gftt_peaks_strip(const Gft
 //
 // Rows are read by the lanes themselves, three ahead, not staged: the strip
 // needs no LDS but its candidates, and four wavefronts to a SIMD hide what is
-// left of the latency (staged through LDS, two: 177 us for the 60 Mpx below).
+// left of the latency (staged through LDS, two, which took 1.2 times as long).
 //
-// VALU issue bounds large calls, a row's latency the small ones.  About 105
-// instruction slots a row and 124 pixels against 82 a row and 60 pixels of the
-// one-column binary64 walk: 64 mixed frames (60 Mpx) 206 us before, 124 us now;
-// one 752x480 frame 19.4 us before, 11 us now.
+// A row's latency bounds small calls; in large ones issue takes over, with the
+// rows whose bounds stay open.  About 105 instruction slots a row and 124 pixels
+// against 82 a row and 60 pixels of the one-column binary64 walk: 64 mixed
+// frames (60 Mpx) 207 us with that walk, 159 us with this one; one 752x480 frame
+// 19.9 us, 12.0 us.
 
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
@@ -663,7 +666,7 @@ __global__ __launch_bounds__(64) void k_gftt_peaks_pair(const GfttJob *__restric
     // The buffer's candidates: their exact responses, 64 at a time and in place,
     // then the peaks to one range of the list (one atomic: the counter is the
     // frame's, and atomics on a counter's line take turns: with one for every 64
-    // candidates the mixed 64-frame walk took 194 us, with one for 384 162 us).
+    // candidates the mixed 64-frame walk took 1.2 times as long as with one for 384).
     auto resolve = [&]() {
         uint32_t n = 0;
         __builtin_amdgcn_wave_barrier();                        // entries of the other lanes

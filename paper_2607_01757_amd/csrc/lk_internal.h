@@ -177,10 +177,10 @@ constexpr int64_t kGfttTallPixels = int64_t(8) << 20;
 // offsets).
 constexpr int kGfttPairW = 124;
 // Strip height of that walk: a strip pays six rows of halo and two atomics, so
-// strips grow as soon as the chip is full of them (frames of 752x480, us at
-// heights 8 / 16 / 32 / 64: 1 frame 11.9 / 12.2 / 18 / 32, 3 frames 21 / 17 / 20
-// / 32, 12 frames 91 / 33 / 33 / 36, 24 frames 181 / 72 / 35 / 45, 64 frames
-// 342 / 200 / 89 / 68).
+// strips grow as soon as the chip is full of them (whole detections of textured
+// 752x480 frames, us at heights 8 / 16 / 32 / 64: 1 frame 28.7 / 31.3 / 38.4 /
+// 52.1, 3 frames 38.5 / 34.6 / 39.7 / 51.5, 12 frames 121 / 49.2 / 48.7 / 53.6,
+// 24 frames 187 / 93.6 / 55.7 / 65.0, 64 frames 339 / 216 / 126 / 108).
 inline int gftt_pair_height(int64_t pixels)
 {
     return pixels < (3 << 18) ? 8 : (pixels < (3 << 19) ? 16 : (pixels < (3 << 22) ? 32 : 64));

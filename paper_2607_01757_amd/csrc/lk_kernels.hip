@@ -1454,15 +1454,18 @@ struct Baton {
 };
 
 // One coarse-to-fine pass of pyramid I (template) into pyramid J (target).
-// LV (own < 0: off): the levels of the pass belong to the wavefronts of one
-// workgroup, this one's is `own`.  A level's template and normal matrix depend
-// on the point alone, so every wavefront forms its own at once and then waits
-// for the coarser level's flow; wavefront `own` passes own workgroup barriers
-// after its turn and L - 1 - own before it, one per level in all.  Every
-// wavefront returns the pass's result.  While it waits, a wavefront brings the
-// target taps around the expected window into LDS: (aheadx, aheady) is the
-// flow to expect at level 0; with `refine` a level takes that of the level two
-// above it instead, once known.  The expectation moves no result.
+// LV: the levels of the pass belong to the wavefronts of one workgroup, this
+// one's is `own` (unused otherwise).  A level's template and normal matrix
+// depend on the point alone, so every wavefront forms its own at once and then
+// waits for the coarser level's flow.  A wavefront passes L workgroup barriers
+// in all: L - 1 - own before its turn and own + 1 after it, the last of which
+// also parts this pass's reads of the batons from the next pass's writes (for L
+// >= 2).  Only a point outside level 0 returns without them, in every
+// wavefront.  Every wavefront returns the pass's result.  While it waits, a
+// float32 wavefront brings the target taps around the expected window into LDS:
+// (aheadx, aheady) is the flow to expect at level 0; with `refine` a level
+// takes that of the level two above it instead, once known.  The expectation
+// moves no result.
 template <int ST, class G, bool LV = false>
 __device__ PassResult run_pass(const PyrDesc &I, const PyrDesc &J, float px, float py, float gx, float gy,
                                const TrackArgs &a, const LaneCfg &lc, int lane, float *lds, int32_t *iters,
