@@ -599,8 +599,10 @@ __global__ __launch_bounds__(64 * kStripWaves) void k_gftt_peaks_strip(const Gft
 // needs no LDS but its candidates, and four wavefronts to a SIMD hide what is
 // left of the latency (staged through LDS, two, which took 1.2 times as long).
 //
-// A row's latency bounds small calls; in large ones issue takes over, with the
-// rows whose bounds stay open.  About 105 instruction slots a row and 124 pixels
+// A row's latency bounds small calls.  In large ones no one unit is full: 64
+// frames of 51 Mpx are 7112 strips on 4096 places, so the second round fills
+// three quarters of them (VALU busy 0.58, 2.5 wavefronts a SIMD on average, a
+// third of their time in waits).  About 105 instruction slots a row and 124 pixels
 // against 82 a row and 60 pixels of the one-column binary64 walk: 64 mixed
 // frames (60 Mpx) 207 us with that walk, 159 us with this one; one 752x480 frame
 // 19.9 us, 12.0 us.
