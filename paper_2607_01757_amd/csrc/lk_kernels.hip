@@ -2036,28 +2036,37 @@ template <class G>
 inline unsigned blocks_for(long waves) { return (unsigned)((waves + G::WPB - 1) / G::WPB); }
 
 // Whether a launch of n keypoints takes a wavefront per level: when all their
-// workgroups are resident at once.  Up to there the side-by-side templates
-// shorten the launch; past it the waiting wavefronts hold room that a second
-// round of workgroups needs.  Three wavefronts leave out one SIMD of the four,
-// so with 3 levels the last slot of a CU is not counted on.  Measured (us,
-// wavefront per level against one wavefront per keypoint, back to back, no
-// backward pass; `lost`: the target is an unrelated frame and the points take
-// every iteration, which leaves nothing to gain): 21x21 float32, 3 levels: 11.0
-// / 14.4 at 100 keypoints, 14.8 / 18.3 at 1280 (the limit; lost 72.1 / 72.8);
-// 4 levels 12.4 / 19.0 at 256, 14.8 / 21.2 at 1024 (the limit; lost 85.8 /
-// 87.4); 2 levels 14.0 / 13.9 at 2048 (the limit; lost 54.6 / 54.2); 21x21
-// binary16, 3 levels: 13.2 / 14.9 at 1024, 15.2 / 16.1 at 1792 (the limit; lost
-// 75.0 / 73.8), lost 80.0 / 74.9 at 2048; 31x31 binary16, 3 levels: 16.7 / 20.6
-// at 768 (the limit; lost 93.3 / 94.3), lost 110.5 / 95.4 at 1024; 31x31
-// float32, 4 levels: 17.4 / 34.1 at 256, 18.1 / 34.0 at 512 (the limit; lost
-// 108 / 121).  (256: the CUs of an MI355X.)
+// workgroups are resident at once and a sixth of the chip stays free.  Up to
+// there the side-by-side templates shorten the launch; past it the waiting
+// wavefronts hold room that a second round of workgroups, or another stream's
+// launch, needs.  Three wavefronts leave out one SIMD of the four, so with 3
+// levels the last place of a CU is not counted on.  (The float32 kernels of
+// windows up to 21 hold more wavefronts than they are built for: their 16 a CU
+// are under two thirds.)  Measured (us, wavefront per level against one
+// wavefront per keypoint, back to back, no backward pass; `lost`: the target is
+// an unrelated frame and the points take every iteration, which leaves nothing
+// to gain): 21x21 float32, 3 levels: 11.0 / 14.4 at 100 keypoints, 14.8 / 18.3 at
+// 1280 (the limit; lost 72.1 / 72.8); 4 levels 12.4 / 19.0 at 256, 14.8 / 21.2 at
+// 1024 (the limit; lost 85.8 / 87.4); 2 levels 14.0 / 13.9 at 2048 (the limit;
+// lost 54.6 / 54.2); 21x21 binary16, 3 levels: 13.2 / 14.9 at 1024, lost 80.0 /
+// 74.9 at 2048; 31x31 binary16, 3 levels: 16.7 / 20.6 at 768 (the limit; lost
+// 93.3 / 94.3), lost 110.5 / 95.4 at 1024; 31x31 float32, 4 levels: 17.4 / 34.1
+// at 256.  Four streams at once, times of a wavefront per keypoint: 31x31
+// binary16, 4 levels, backward pass: 0.78 at 384 keypoints, 1.05 at 640 (the
+// limit), 1.15 at 768; 15x15 binary16, 4 levels 0.94 at 768, 0.99 at 1280 (the
+// limit), 1.13 at 1536; 31x31 float32, 2 levels 0.83 at 512, 0.95 at 768 (the
+// limit), 1.23 at 1024; lost points stay within 1.2 (31x31 float32 with 3 levels
+// 1.33 at its limit of 512).  (256: the CUs of an MI355X.)
 constexpr int kCUs = 256;
 
 template <int ST, class G>
 inline bool use_level_waves(const TrackArgs &a)
 {
-    const int slots = 4 * kLevelOcc<ST, G> - (a.levels == 3 ? 1 : 0);      // wavefronts of a CU
-    return a.levels >= 2 && a.levels <= kLevelWaves && a.n <= kCUs * (slots / a.levels);
+    if (a.levels < 2 || a.levels > kLevelWaves) return false;
+    constexpr int places = 4 * kLevelOcc<ST, G>;                           // wavefronts of a CU
+    constexpr int used = ST == LK_STORAGE_F32 && G::R <= 7 ? places : places * 5 / 6;
+    const int resident = (places - (a.levels == 3 ? 1 : 0)) / a.levels;    // workgroups of a CU
+    return a.n <= kCUs * resident && a.n <= kCUs * used / a.levels;
 }
 
 template <int ST, class G>

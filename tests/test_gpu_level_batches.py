@@ -17,7 +17,8 @@ FILL = 3200                      # points that move a launch past every limit
 @pytest.mark.parametrize("in_place", [False, True])
 @pytest.mark.parametrize("win,levels,f16,n", [
     (21, 2, 0, 2048), (21, 3, 0, 1280), (21, 3, 0, 1281), (21, 4, 0, 1024), (9, 3, 0, 600),
-    (21, 3, 1, 1792), (21, 3, 1, 1793), (15, 4, 1, 1536), (31, 3, 1, 768), (31, 3, 1, 769), (31, 2, 0, 1024)])
+    (21, 3, 1, 1706), (21, 3, 1, 1707), (15, 4, 1, 1280), (31, 3, 1, 768), (31, 4, 1, 640), (31, 4, 1, 641),
+    (31, 2, 0, 768), (31, 3, 0, 512)])
 def test_batches(win, levels, f16, n, in_place):
     import torch
     from paper_2607_01757_amd import lk
