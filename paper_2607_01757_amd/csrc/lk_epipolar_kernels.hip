@@ -284,9 +284,12 @@ __device__ __forceinline__ bool epi_inlier(const double (&F)[9], float px, float
     return (den > 0.0) & (num * num <= thr2 * den);
 }
 
-__global__ __launch_bounds__(kEpiLanes * kEpiWaves) void k_epi_hypotheses(const EpiJob *__restrict__ jobs,
-                                                                          const int32_t *__restrict__ wg_job,
-                                                                          double thr2)
+// Three wavefronts a SIMD: the slab leaves room for three workgroups in a CU,
+// one wavefront of each to a SIMD, and at 169 registers only two fitted (768
+// workgroups, 8 correspondences 75 us a call against 60; 16384 workgroups 1010
+// against 882).
+__global__ __launch_bounds__(kEpiLanes * kEpiWaves) __attribute__((amdgpu_waves_per_eu(3)))
+void k_epi_hypotheses(const EpiJob *__restrict__ jobs, const int32_t *__restrict__ wg_job, double thr2)
 {
     __shared__ double sa[72 * kEpiLanes];
     __shared__ int scol[9 * kEpiLanes];
@@ -300,7 +303,11 @@ __global__ __launch_bounds__(kEpiLanes * kEpiWaves) void k_epi_hypotheses(const 
     const bool live = k < J.h;
     double F[9];
     if (wv == 0) {
-        const bool solved = live && epi_model(J, J.samples + 8 * k, sa, scol, lane, F);
+        // (a lane of its own for the solve: the scoring's addresses formed of `lane`
+        // would be held through it)
+        int ln = lane;
+        asm("" : "+v"(ln));
+        const bool solved = live && epi_model(J, J.samples + 8 * k, sa, scol, ln, F);
         if (solved)
 #pragma unroll
             for (int j = 0; j < 9; ++j) slab(sa, 0, j, lane) = F[j];

@@ -46,6 +46,14 @@ def test_detector_does_not_spill(kernels, kernel):
     assert spills(kernels, r"\d" + kernel) == {}
 
 
+def test_epipolar_fills_a_cu(kernels):
+    """Three workgroups of four wavefronts share a CU (LDS holds three): a SIMD
+    has 512 registers for one wavefront of each, granted eight at a time."""
+    assert spills(kernels, r"\dk_epi_(hypotheses|best)") == {}
+    (k,) = [k for n, k in kernels.items() if "k_epi_hypotheses" in n]
+    assert 3 * (-(-k[".vgpr_count"] // 8) * 8) <= 512 and 3 * k[".group_segment_fixed_size"] <= 160 * 1024
+
+
 def test_no_level_kernel_without_a_launch(kernels):
     """The launch by levels exists for the default shapes only: no kernel of it
     is built for the 2 and 4 keypoints a workgroup that a program can ask for."""
